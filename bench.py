@@ -64,17 +64,6 @@ def recorded_traffic(kernel: str):
     return rec["traffic_bytes_per_launch"]
 
 
-def bulk_span_rows(tile_bytes: int) -> int:
-    """The copy kernel's span (1 KiB rows per wavefront) for a bulk launch:
-    the power of two at or above a quarter of the tile, within [2, 32]
-    (mirrors the library's launch configuration, for labelling only)."""
-    quarter = -(-tile_bytes // 4096)
-    span = 2
-    while span < 32 and span < quarter:
-        span *= 2
-    return span
-
-
 def percentile(xs, q):
     """The q-th percentile (0-100) of xs, linear between order statistics."""
     v = sorted(xs)
@@ -194,7 +183,7 @@ def main():
     per_launch_us = s1_avg_us / launches
     achieved = per_launch_bytes / (per_launch_us * 1e-6) / 1e9
     downtimes = [d for _, d in runs]
-    kernel_name = "copy_tiles<0, 0, %d, %d>" % (ids_mode, bulk_span_rows(src.tile_bytes))
+    kernel_name = "copy_rows<0, 0, %d, 1>" % ids_mode
 
     # GPU time of every stage's copy (events around its launches), in extra
     # migrations outside the timed region: within the timed steps only stage

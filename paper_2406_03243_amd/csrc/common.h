@@ -45,7 +45,7 @@ struct LaunchEvents {
     hipEvent_t stop = nullptr;
 };
 
-// Launch k of `launches` of one call.
+// Launch k of `launches` of one call (launches -1: not the last one).
 hipError_t launch_kernel(const void *fn, dim3 grid, dim3 block, void **args, hipStream_t stream,
                          const LaunchEvents &ev, int64_t k, int64_t launches)
 {

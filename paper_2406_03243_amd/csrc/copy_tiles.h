@@ -7,18 +7,46 @@
 // (l, kv) of block dst[i] (pool to pool), or in slot ((l * 2 + kv) * n + i)
 // of a contiguous staging buffer (pack), or the reverse (unpack).
 //
-// Kernel design (CDNA4, wave64):
-//  * The work of a call is a list of tiles, one per (pair, layer, K/V); a
-//    tile is tile_bytes contiguous bytes on both sides.  A tile is cut into
-//    SPAN-KiB spans and each span is one wavefront's work item: the wave
-//    issues SPAN 1-KiB loads (64 lanes x 16 bytes) before its first store,
-//    so each lane keeps SPAN x 16 bytes in flight and the wave streams one
-//    contiguous span in and out.  SPAN is about a quarter of the tile, so
-//    the four wavefronts of a workgroup move one whole tile: measured on
-//    MI355X, long per-wave spans beat interleaving the wavefronts over
-//    shared 4 KiB rows by 5-16% (128 KiB tiles: 32 KiB spans, 6.1-6.3
-//    against 5.3-5.4 TB/s).  Launches with few items (a final stage) use
-//    2 KiB spans so their tiles spread over more CUs.
+// Two kernels, chosen by whether the caller caps the grid:
+//
+// copy_rows, every uncapped launch.  A call's bytes are a list of 1 KiB rows
+// (64 lanes x 16 bytes); a workgroup is one wavefront and moves one row: one
+// load and one store per lane.
+//  * What bounds it is HBM, and how well DRAM likes the order in which a
+//    launch touches it.  With one row per wavefront the rows in flight at any
+//    time (32 wavefronts a CU, 8 MiB over the chip) are consecutive in the
+//    launch's order, so they fall into few DRAM pages; with more rows per
+//    wavefront each wavefront walks a run of its own and the same bytes in
+//    flight are spread over thousands of runs.  Measured on MI355X, one
+//    process, read + written bytes, 4 / 32 / 52 / 128 KiB tiles: 1 row 6.5 /
+//    6.7 / 6.7 / 6.85 TB/s, 2 rows 6.1 / 5.8 / 6.2 / 6.2, 4 rows 5.6 / 5.5 /
+//    5.7 / 5.8; spans of a quarter tile walked pair by pair (copy_tiles, what
+//    ran before) 5.0 / 5.1 / 5.7 / 6.25.
+//  * The order is plane-major: all pairs of one (layer, K/V) tensor, then
+//    the next tensor.  Pair-major order spreads neighbouring rows over 2 *
+//    num_layers tensors (4 KiB tiles: 5.0 against 5.9-6.3 TB/s).
+//  * The pairs of a bulk launch with ids on the host are sorted by
+//    destination block, so that the writes of a tensor sweep it upwards:
+//    +2-9% over random pairs on tiles up to 64 KiB, +1% on 128 KiB (sorting
+//    by source instead gains half of that or less).  The order of the pairs
+//    is free: no destination block occurs twice in a call.
+//  * Consecutive rows go to the eight XCDs in turn, the dispatcher's own
+//    order, for tiles below 128 KiB; from there on each XCD takes runs of
+//    kXcdRun rows (128 KiB tiles 6.63 -> 6.84, 256 KiB 6.75 -> 6.81, but
+//    64 KiB 6.69 -> 6.66 and 32 KiB 6.66 -> 6.44 TB/s).
+//  * A launch of at most one round of resident wavefronts (a final stage of
+//    a block or so) moves two rows per wavefront: it has no DRAM order to
+//    keep, and half as many wavefronts to dispatch (one block of 60 layers of
+//    52 KiB tiles 4.87 against 5.10 us, of 80 layers of 32 KiB 4.27 against
+//    4.63 us, of 32 layers of 128 KiB 5.03 against 5.09 us).
+//
+// copy_tiles, launches under a workgroup cap (the throttle of a migration's
+// non-final stages).  Few resident workgroups walk the items, so each must
+// keep many bytes in flight by itself:
+//  * A tile is cut into SPAN-KiB spans and each span is one wavefront's work
+//    item: the wave issues SPAN 1-KiB loads before its first store.  SPAN is
+//    about a quarter of the tile, so the four wavefronts of a workgroup move
+//    one whole tile.  Items run pair-major.
 //  * Every span runs the same unpredicated sequence of SPAN loads and SPAN
 //    stores.  A row of the span that lies past the end of the tile (the
 //    last span of a tile that is not a whole number of spans, such as the
@@ -27,14 +55,9 @@
 //    zeros for its load and drops its store.  Predicating those rows on
 //    the lane mask instead makes the compiler wait for every earlier memory
 //    operation before each store of the span (it cannot count them across
-//    the branches), which serialised the tail's stores.  Measured on 52 KiB
-//    tiles in one process, alternating: predicated rows 0.62 of HBM peak; a
-//    separate, range-checked code path for short spans only 0.67-0.68; one
-//    sequence for every span 0.72-0.75 (128 and 32 KiB tiles gained about
-//    1%).
-//  * Wave items run pair-major (all spans of all layers of one block pair,
-//    then the next pair); one workgroup per four items unless the grid is
-//    capped, in which case resident workgroups walk the items.
+//    the branches), which serialised the tail's stores.
+//
+// Both:
 //  * The block ids of an item are wavefront-uniform; they and the per-layer
 //    base addresses are read with scalar loads, so the only vector memory
 //    traffic is the copy itself.
@@ -52,11 +75,13 @@
 //    cache policy: non-temporal loads, and stores that are non-temporal
 //    with the sc1 scope bit (device scope on gfx950).  Every byte is touched
 //    once, and streaming it past the caches leaves them to the decode work
-//    beside the migration.
+//    beside the migration.  (copy_rows, 32 KiB tiles: 6.43 TB/s; cached
+//    loads 6.12, plain stores 5.5, sc1 stores without nt 5.7.)
 #pragma once
 
 #include <algorithm>
 #include <cstring>
+#include <vector>
 
 #include "common.h"
 
@@ -66,8 +91,11 @@ enum Side { kPool = 0, kLinear = 1 };
 
 
 // Arguments of one copy launch.  Pool sides address tile (l, kv, id) at
-// tab[kv * L + l] + id * tile_bytes; linear sides address pair i of plane
-// (l, kv) at lin + ((l * 2 + kv) * lin_pairs + lin_first + i) * tile_bytes.
+// tab[kv * L + l] + id * tile_bytes; linear sides address tile x of plane
+// (l, kv) at lin + ((l * 2 + kv) * lin_pairs + x) * tile_bytes.  For pair i
+// of the launch, x is lin_first + i, or, for a linear source whose pairs
+// were sorted, the pair's place in the call, which then rides as its source
+// id (kIds32).
 struct CopyArgs {
     const uint64_t *src_tab;
     const uint64_t *dst_tab;
@@ -81,6 +109,8 @@ struct CopyArgs {
     uint32_t pairs;             // pairs in this launch
     uint32_t spans_per_tile;
     uint32_t items;             // wave items: pairs * planes * spans_per_tile
+    uint32_t first_item;        // this launch's first item (copy_rows)
+    uint32_t xcd_runs;          // copy_rows: 1 if each XCD takes runs of kXcdRun items
     uint32_t lin_first;         // this launch's first pair within the whole call
     uint32_t lin_pairs;         // pairs in the whole call
     uint32_t ids[2 * kInlinePairs]; // inline ids, laid out as the launch's Ids mode says
@@ -117,7 +147,59 @@ __device__ __forceinline__ uint32_t dst_id(const CopyArgs &a, uint32_t i)
     return IDS == kIds32 ? a.ids[kInlinePairs + i] : static_cast<uint32_t>(id_entry(a.dst_ids_dev, i));
 }
 
-template <int SRC, int DST, int IDS, int SPAN>
+// Workgroups (rows) in a row on one XCD under xcd_runs: 512 KiB.
+constexpr uint32_t kXcdRun = 512;
+
+// One wavefront per workgroup, one item of ROWS KiB of a tile each.
+template <int SRC, int DST, int IDS, int ROWS>
+__global__ void __launch_bounds__(64) copy_rows(const CopyArgs a)
+{
+    uint32_t w = blockIdx.x;
+    if (a.xcd_runs) {
+        // the dispatcher hands workgroup g to XCD g % 8: renumbered so that
+        // the k-th kXcdRun workgroups of an XCD are consecutive items (the
+        // grid's tail keeps the plain order)
+        const uint32_t round = w / (8u * kXcdRun), r = w % (8u * kXcdRun);
+        if ((round + 1u) * (8u * kXcdRun) <= gridDim.x)
+            w = round * (8u * kXcdRun) + (r % 8u) * kXcdRun + r / 8u;
+    }
+    const uint32_t item = a.first_item + w;
+    const uint32_t tile = item / a.spans_per_tile;
+    const uint32_t span = item - tile * a.spans_per_tile;
+    const uint32_t plane = tile / a.pairs;      // layer * 2 + kv
+    const uint32_t i = tile - plane * a.pairs;
+    const uint32_t layer = plane >> 1, kv = plane & 1u;
+
+    const uint8_t *s;
+    uint8_t *d;
+    if (SRC == kPool) {
+        s = reinterpret_cast<const uint8_t *>(table_entry(a.src_tab, kv * a.num_layers + layer)) +
+            static_cast<uint64_t>(uniform(src_id<IDS>(a, i))) * a.tile_bytes;
+    } else {
+        const uint32_t x = IDS == kIdsDevice ? a.lin_first + i : uniform(src_id<IDS>(a, i));
+        s = a.src_lin + (static_cast<uint64_t>(plane) * a.lin_pairs + x) * a.tile_bytes;
+    }
+    if (DST == kPool) {
+        d = reinterpret_cast<uint8_t *>(table_entry(a.dst_tab, kv * a.num_layers + layer)) +
+            static_cast<uint64_t>(uniform(dst_id<IDS>(a, i))) * a.tile_bytes;
+    } else {
+        d = a.dst_lin + (static_cast<uint64_t>(plane) * a.lin_pairs + a.lin_first + i) * a.tile_bytes;
+    }
+
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(s, a.tile_bytes);
+    const __amdgpu_buffer_rsrc_t rd = tile_rsrc(d, a.tile_bytes);
+    const uint32_t first = span * ROWS * kWaveRow, lane_off = threadIdx.x * 16u;
+    u32x4 r[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u)
+        r[u] = buffer_load16(rs, row_offset(first + u * kWaveRow, a.tile_bytes) + lane_off);
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u)
+        buffer_store16(rd, row_offset(first + u * kWaveRow, a.tile_bytes) + lane_off, r[u]);
+}
+
+// Pool to pool, ids in the kernel arguments.
+template <int IDS, int SPAN>
 __global__ void __launch_bounds__(kThreads) copy_tiles(const CopyArgs a)
 {
     const uint32_t lane_off = (threadIdx.x % 64) * 16u;
@@ -129,21 +211,10 @@ __global__ void __launch_bounds__(kThreads) copy_tiles(const CopyArgs a)
         const uint32_t i = tile / a.planes;
         const uint32_t plane = tile - i * a.planes; // layer * 2 + kv
         const uint32_t layer = plane >> 1, kv = plane & 1u;
-
-        const uint8_t *s;
-        uint8_t *d;
-        if (SRC == kPool) {
-            s = reinterpret_cast<const uint8_t *>(table_entry(a.src_tab, kv * a.num_layers + layer)) +
-                static_cast<uint64_t>(uniform(src_id<IDS>(a, i))) * a.tile_bytes;
-        } else {
-            s = a.src_lin + (static_cast<uint64_t>(plane) * a.lin_pairs + a.lin_first + i) * a.tile_bytes;
-        }
-        if (DST == kPool) {
-            d = reinterpret_cast<uint8_t *>(table_entry(a.dst_tab, kv * a.num_layers + layer)) +
-                static_cast<uint64_t>(uniform(dst_id<IDS>(a, i))) * a.tile_bytes;
-        } else {
-            d = a.dst_lin + (static_cast<uint64_t>(plane) * a.lin_pairs + a.lin_first + i) * a.tile_bytes;
-        }
+        const uint8_t *s = reinterpret_cast<const uint8_t *>(table_entry(a.src_tab, kv * a.num_layers + layer)) +
+                           static_cast<uint64_t>(uniform(src_id<IDS>(a, i))) * a.tile_bytes;
+        uint8_t *d = reinterpret_cast<uint8_t *>(table_entry(a.dst_tab, kv * a.num_layers + layer)) +
+                     static_cast<uint64_t>(uniform(dst_id<IDS>(a, i))) * a.tile_bytes;
 
         const __amdgpu_buffer_rsrc_t rs = tile_rsrc(s, a.tile_bytes);
         const __amdgpu_buffer_rsrc_t rd = tile_rsrc(d, a.tile_bytes);
@@ -181,39 +252,113 @@ int bulk_span(uint32_t tile_bytes)
     return span;
 }
 
-template <int SRC, int DST, int IDS>
+template <int IDS>
 const void *copy_kernel_span(int span)
 {
     switch (span) {
     case 32:
-        return reinterpret_cast<const void *>(&copy_tiles<SRC, DST, IDS, 32>);
+        return reinterpret_cast<const void *>(&copy_tiles<IDS, 32>);
     case 16:
-        return reinterpret_cast<const void *>(&copy_tiles<SRC, DST, IDS, 16>);
+        return reinterpret_cast<const void *>(&copy_tiles<IDS, 16>);
     case 8:
-        return reinterpret_cast<const void *>(&copy_tiles<SRC, DST, IDS, 8>);
+        return reinterpret_cast<const void *>(&copy_tiles<IDS, 8>);
     case 4:
-        return reinterpret_cast<const void *>(&copy_tiles<SRC, DST, IDS, 4>);
+        return reinterpret_cast<const void *>(&copy_tiles<IDS, 4>);
     default:
-        return reinterpret_cast<const void *>(&copy_tiles<SRC, DST, IDS, 2>);
+        return reinterpret_cast<const void *>(&copy_tiles<IDS, 2>);
     }
 }
 
-template <int SRC, int DST>
-const void *copy_kernel(int ids, int span)
+template <int SRC, int DST, int IDS>
+const void *copy_kernel_rows(int rows)
 {
-    if (ids == kIdsDevice)
-        return copy_kernel_span<SRC, DST, kIdsDevice>(span);
-    if (SRC == kPool && DST == kPool && ids == kIds16)
-        return copy_kernel_span<SRC, DST, kIds16>(span);
-    return copy_kernel_span<SRC, DST, kIds32>(span);
+    return rows == 2 ? reinterpret_cast<const void *>(&copy_rows<SRC, DST, IDS, 2>)
+                     : reinterpret_cast<const void *>(&copy_rows<SRC, DST, IDS, 1>);
 }
 
-// A launch with fewer wave items than this per CU is small (a final stage).
-constexpr uint32_t kBulkWaveItemsPerCU = 16;
+template <int SRC, int DST>
+const void *copy_kernel(int ids, int rows)
+{
+    if (ids == kIdsDevice)
+        return copy_kernel_rows<SRC, DST, kIdsDevice>(rows);
+    if (SRC == kPool && DST == kPool && ids == kIds16)
+        return copy_kernel_rows<SRC, DST, kIds16>(rows);
+    return copy_kernel_rows<SRC, DST, kIds32>(rows);
+}
 
-// max_workgroups > 0 caps the grid: fewer, resident workgroups walk the
-// items, leaving the rest of the chip (and of HBM) to other work.
-// ids16: every id of both lists is below 65536 (pool to pool only).
+// Tiles from this size on are walked in runs of kXcdRun rows per XCD.
+constexpr uint32_t kXcdRunTileBytes = 128u << 10;
+// Resident wavefronts of a full CU; a launch of fewer rows than this per CU
+// is small (a final stage).
+constexpr uint32_t kWavesPerCU = 32;
+// Capped launches: fewer wave items than this per CU take 2 KiB spans.
+constexpr uint32_t kBulkWaveItemsPerCU = 16;
+// Rows per launch: 64 lanes each, in 32-bit work-item counts.
+constexpr uint32_t kMaxRowsPerLaunch = 1u << 24;
+// Calls of fewer pairs keep the caller's order (too few to be neighbours).
+constexpr int64_t kSortPairs = 32;
+
+// Sorts the pairs of a call by destination id: out[k] = (source, destination)
+// as one word, source in the low half.  src null: the source of pair k is k.
+// A least-significant-digit radix sort, 11 bits a pass (two passes for 16-bit
+// ids), which leaves 512 pairs sorted in 2-3 us.
+void sort_pairs(const int32_t *src, const int32_t *dst, int64_t n, std::vector<uint64_t> &out)
+{
+    constexpr int kBits = 11;
+    constexpr uint32_t kMask = (1u << kBits) - 1;
+    std::vector<uint64_t> tmp(static_cast<size_t>(n));
+    out.resize(static_cast<size_t>(n));
+    uint32_t hi = 0;
+    for (int64_t k = 0; k < n; ++k) {
+        hi |= static_cast<uint32_t>(dst[k]);
+        out[static_cast<size_t>(k)] = static_cast<uint64_t>(static_cast<uint32_t>(dst[k])) << 32 |
+                                      static_cast<uint32_t>(src ? src[k] : static_cast<int32_t>(k));
+    }
+    for (int shift = 0; shift < 32 && (hi >> shift) != 0; shift += kBits) {
+        uint32_t at[kMask + 1] = {};
+        for (uint64_t v : out)
+            ++at[static_cast<uint32_t>(v >> (32 + shift)) & kMask];
+        uint32_t sum = 0;
+        for (uint32_t &c : at) {
+            const uint32_t here = c;
+            c = sum;
+            sum += here;
+        }
+        for (uint64_t v : out)
+            tmp[at[static_cast<uint32_t>(v >> (32 + shift)) & kMask]++] = v;
+        out.swap(tmp);
+    }
+}
+
+// Puts pairs [first, first + m) of a call into a launch's inline ids.  src
+// null (a staging source): the pair's place in the call takes its place;
+// dst null (a staging destination): none.
+inline void inline_ids(uint32_t *ids, int mode, const int32_t *src, const int32_t *dst,
+                       const std::vector<uint64_t> &sorted, int64_t first, uint32_t m)
+{
+    for (uint32_t k = 0; k < m; ++k) {
+        const int64_t j = first + k;
+        uint32_t s, d;
+        if (!sorted.empty()) {
+            s = static_cast<uint32_t>(sorted[static_cast<size_t>(j)]);
+            d = static_cast<uint32_t>(sorted[static_cast<size_t>(j)] >> 32);
+        } else {
+            s = static_cast<uint32_t>(src ? src[j] : static_cast<int32_t>(j));
+            d = dst ? static_cast<uint32_t>(dst[j]) : 0u;
+        }
+        if (mode == kIds16) {
+            ids[k] = s | d << 16;
+        } else {
+            ids[k] = s;
+            ids[kInlinePairs + k] = d;
+        }
+    }
+}
+
+// max_workgroups > 0 caps the grid (pool to pool with host ids only): fewer,
+// resident workgroups walk the items, leaving the rest of the chip (and of
+// HBM) to other work.  ids16: every id of both lists is below 65536 (pool to
+// pool only).  Throws nothing.
 template <int SRC, int DST>
 int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int64_t n,
                 bool ids_on_device, hipStream_t stream, uint32_t max_workgroups = 0, bool ids16 = false,
@@ -221,24 +366,40 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
 {
     const int ids = ids_on_device ? kIdsDevice : (SRC == kPool && DST == kPool && ids16) ? kIds16 : kIds32;
     const int64_t inline_pairs = ids == kIds16 ? 2 * kInlinePairs : kInlinePairs;
-    int span = bulk_span(a.tile_bytes);
-    uint32_t spt = (a.tile_bytes + span * kWaveRow - 1) / (span * kWaveRow);
+    const bool capped = SRC == kPool && DST == kPool && max_workgroups > 0 && !ids_on_device;
     const uint64_t pairs_first_launch = std::min<int64_t>(n, ids_on_device ? n : inline_pairs);
-    if (pairs_first_launch * 2ull * a.num_layers * spt < kBulkWaveItemsPerCU * compute_units()) {
+    const uint64_t planes = 2ull * a.num_layers;
+    auto spans = [&](int kib) { return (a.tile_bytes + kib * kWaveRow - 1) / (kib * kWaveRow); };
+    int span = 1;
+    if (capped) {
+        span = bulk_span(a.tile_bytes);
+        if (pairs_first_launch * planes * spans(span) < kBulkWaveItemsPerCU * compute_units())
+            span = 2;
+    } else if (pairs_first_launch * planes * spans(1) <= kWavesPerCU * compute_units()) {
         span = 2;
-        spt = (a.tile_bytes + span * kWaveRow - 1) / (span * kWaveRow);
     }
-    a.spans_per_tile = spt;
-    const uint64_t items_per_pair = 2ull * a.num_layers * spt;
-    uint64_t per_launch = std::min<uint64_t>(0x7fffffffull / items_per_pair,
-                                             ids_on_device ? UINT64_MAX : static_cast<uint64_t>(inline_pairs));
+    a.spans_per_tile = spans(span);
+    const uint64_t items_per_pair = planes * a.spans_per_tile;
+    const uint64_t per_launch = std::min<uint64_t>(0x7fffffffull / items_per_pair,
+                                                   ids_on_device ? UINT64_MAX : static_cast<uint64_t>(inline_pairs));
     if (per_launch == 0)
         return LLMIG_EINVAL;
+    std::vector<uint64_t> sorted;
+    if (!capped && span == 1 && DST == kPool && ids != kIdsDevice && n >= kSortPairs) {
+        try {
+            sort_pairs(src_ids, dst_ids, n, sorted);
+        } catch (...) {
+            sorted.clear();     // no memory for it: the caller's order
+        }
+    }
     a.lin_pairs = static_cast<uint32_t>(n);
-    a.planes = 2u * a.num_layers;
-    const void *fn = copy_kernel<SRC, DST>(ids, span);
-    const int64_t launches = (n + static_cast<int64_t>(per_launch) - 1) / static_cast<int64_t>(per_launch);
-    for (int64_t first = 0, k = 0; first < n; first += static_cast<int64_t>(per_launch), ++k) {
+    a.planes = static_cast<uint32_t>(planes);
+    a.xcd_runs = a.tile_bytes >= kXcdRunTileBytes ? 1u : 0u;
+    const void *fn = !capped          ? copy_kernel<SRC, DST>(ids, span)
+                     : ids == kIds16  ? copy_kernel_span<kIds16>(span)
+                                      : copy_kernel_span<kIds32>(span);
+    int64_t launch = 0;
+    for (int64_t first = 0; first < n; first += static_cast<int64_t>(per_launch)) {
         const uint32_t m = static_cast<uint32_t>(std::min<int64_t>(n - first, per_launch));
         a.pairs = m;
         a.lin_first = static_cast<uint32_t>(first);
@@ -246,22 +407,26 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
         if (ids == kIdsDevice) {
             a.src_ids_dev = src_ids ? src_ids + first : nullptr;
             a.dst_ids_dev = dst_ids ? dst_ids + first : nullptr;
-        } else if (ids == kIds16) {
-            for (uint32_t k = 0; k < m; ++k)
-                a.ids[k] = static_cast<uint32_t>(src_ids[first + k]) | (static_cast<uint32_t>(dst_ids[first + k]) << 16);
         } else {
-            if (src_ids)
-                std::memcpy(a.ids, src_ids + first, m * sizeof(int32_t));
-            if (dst_ids)
-                std::memcpy(a.ids + kInlinePairs, dst_ids + first, m * sizeof(int32_t));
+            inline_ids(a.ids, ids, src_ids, dst_ids, sorted, first, m);
         }
         void *args[] = {&a};
-        uint32_t grid = std::min((a.items + kThreads / 64 - 1) / (kThreads / 64), kMaxGridWorkgroups);
-        if (max_workgroups > 0)
-            grid = std::min(grid, max_workgroups);
-        hipError_t e = launch_kernel(fn, dim3(grid), dim3(kThreads), args, stream, ev, k, launches);
-        if (e != hipSuccess)
-            return hip_error(e);
+        const bool last_pairs = first + static_cast<int64_t>(per_launch) >= n;
+        const uint32_t step = capped ? a.items : kMaxRowsPerLaunch;
+        for (uint32_t at = 0; at < a.items; at += std::min(step, a.items - at)) {
+            const uint32_t here = std::min(step, a.items - at);
+            a.first_item = at;
+            uint32_t grid = here, threads = 64;
+            if (capped) {
+                grid = std::min({(here + kThreads / 64 - 1) / (kThreads / 64), kMaxGridWorkgroups, max_workgroups});
+                threads = kThreads;
+            }
+            const bool last = last_pairs && at + here == a.items;
+            hipError_t e = launch_kernel(fn, dim3(grid), dim3(threads), args, stream, ev, launch, last ? launch + 1 : -1);
+            if (e != hipSuccess)
+                return hip_error(e);
+            ++launch;
+        }
     }
     return LLMIG_OK;
 }

@@ -1,0 +1,81 @@
+"""The uncapped tile copy (one 1 KiB row per wavefront) where its dispatch
+turns, byte for byte against the CPU oracle: launches on both sides of the
+small-launch rule, on both sides of the rule that hands each XCD runs of rows
+(whole rounds, a ragged tail, less than one round), pairs sorted by
+destination or too few to be sorted, 16-bit, 32-bit and device ids, several
+launches, tiles that are not whole rows, and staging buffers on either side
+(where sorted pairs carry their place in the buffer)."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import HostPool
+from paper_2406_03243_amd import harness
+from paper_2406_03243_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2406_03243_amd import llmig
+    from paper_2406_03243_amd.llmig import Pool
+
+# layers, blocks, block_size, heads, head_dim, pairs
+CASES = [
+    (1, 40, 16, 32, 128, 31),       # 7936 rows: the small launch; pairs not sorted; under one round of runs
+    (1, 40, 16, 32, 128, 32),       # 8192 rows: the last small launch
+    (1, 40, 16, 32, 128, 33),       # 8448 rows: sorted, two whole rounds and a tail
+    (2, 200, 16, 33, 128, 61),      # 132 KiB tiles: runs that cross tiles, a ragged tail
+    (1, 80, 16, 31, 128, 70),       # 124 KiB tiles: rows dealt in turn
+    (3, 700, 16, 3, 64, 600),       # 6 KiB tiles, 512 + 88 pairs
+    (2, 1500, 8, 5, 40, 1100),      # 3200-byte tiles: a partial last row, three launches
+    (1, 66000, 1, 1, 24, 9000),     # 48-byte tiles, ids past 16 bits
+]
+
+
+def image(pool) -> HostPool:
+    return HostPool(harness.snapshot(pool.k), harness.snapshot(pool.v), pool.block_size, pool.slot_bytes)
+
+
+def pool(shape, seed, purpose):
+    k, v = harness.alloc_layers(shape)
+    total = sum(t.numel() * t.element_size() for t in k + v)
+    harness.fill_bytes_from_host(k + v, wl.random_bytes(seed, purpose, total))
+    return Pool(k, v)
+
+
+def where(ids, dev):
+    return torch.from_numpy(ids).cuda() if dev else ids
+
+
+@pytest.mark.parametrize("dev", [False, True], ids=["host", "device"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"T{c[2] * c[3] * c[4] * 2}_n{c[5]}")
+def test_copy_rows(case, dev):
+    print("[case]", case, dev, flush=True)
+    sys.stdout.flush()
+    layers, blocks, bs, heads, dim, n = case
+    shape = wl.PoolShape(layers, blocks, bs, heads, dim, "fp16")
+    src, dst = pool(shape, 60 + n, wl.SRC_VALUES), pool(shape, 60 + n, wl.DST_VALUES)
+    g = wl.stream(60 + n, wl.EXTRA)
+    ms, md = (g.choice(blocks, n, replace=False).astype(np.int32) for _ in range(2))
+    hs, hd = image(src), image(dst)
+    orc = oracle.default()
+    llmig.llmig_stage(src, dst, where(ms, dev), where(md, dev))
+    torch.cuda.synchronize()
+    orc.copy(hs, hd, ms, md)
+    assert image(dst).equals(hd) and image(src).equals(hs), "stage differs from the oracle"
+    # the same blocks through staging; a gather may repeat a block
+    rep = ms.copy()
+    rep[n // 2] = rep[0]
+    staging = torch.full((n * layers * 2 * src.tile_bytes + 64,), 7, dtype=torch.uint8, device="cuda")
+    llmig.llmig_pack(src, where(rep, dev), staging[:-64])
+    torch.cuda.synchronize()
+    want = orc.pack(hs, rep)
+    assert np.array_equal(staging[:-64].cpu().numpy(), want) and bool((staging[-64:] == 7).all()), "pack differs"
+    into = g.choice(blocks, n, replace=False).astype(np.int32)
+    llmig.llmig_unpack(dst, where(into, dev), staging[:-64])
+    torch.cuda.synchronize()
+    orc.unpack(hd, into, want)
+    assert image(dst).equals(hd), "unpack differs"
