@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 #include "llmig.h"
 
@@ -97,6 +98,9 @@ __device__ __forceinline__ void store16(uint8_t *p, u32x4 v)
 // faster on the LLaMA-7B stage than nt alone (plain or sc0 stores were
 // 2-10% slower).  An access whose offset lies past the resource's
 // num_records is out of range: a load returns zeros and a store is dropped.
+// Tiles are at most 2^31 - 1 bytes, so kOutOfRange plus a lane's offset is
+// always past a tile's resource.
+constexpr uint32_t kOutOfRange = 0x80000000u;
 constexpr int kBufferWord3 = 0x00020000;     // descriptor word 3 for raw 32-bit accesses on gfx9
 constexpr int kStreamLoad = 2;               // nt
 constexpr int kStreamStore = 16 | 2;         // sc1 nt
@@ -114,6 +118,66 @@ __device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
 __device__ __forceinline__ void buffer_store16(__amdgpu_buffer_rsrc_t r, uint32_t off, u32x4 v)
 {
     __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kStreamStore);
+}
+
+// Calls of fewer pairs keep the caller's order (too few to be neighbours).
+constexpr int64_t kSortPairs = 32;
+
+// Sorts the pairs of a call by destination id: out[k] = (source, destination)
+// as one word, source in the low half.  src null: the source of pair k is k.
+// A least-significant-digit radix sort, 11 bits a pass (two passes for 16-bit
+// ids), which leaves 512 pairs sorted in 2-3 us.
+void sort_pairs(const int32_t *src, const int32_t *dst, int64_t n, std::vector<uint64_t> &out)
+{
+    constexpr int kBits = 11;
+    constexpr uint32_t kMask = (1u << kBits) - 1;
+    std::vector<uint64_t> tmp(static_cast<size_t>(n));
+    out.resize(static_cast<size_t>(n));
+    uint32_t hi = 0;
+    for (int64_t k = 0; k < n; ++k) {
+        hi |= static_cast<uint32_t>(dst[k]);
+        out[static_cast<size_t>(k)] = static_cast<uint64_t>(static_cast<uint32_t>(dst[k])) << 32 |
+                                      static_cast<uint32_t>(src ? src[k] : static_cast<int32_t>(k));
+    }
+    for (int shift = 0; shift < 32 && (hi >> shift) != 0; shift += kBits) {
+        uint32_t at[kMask + 1] = {};
+        for (uint64_t v : out)
+            ++at[static_cast<uint32_t>(v >> (32 + shift)) & kMask];
+        uint32_t sum = 0;
+        for (uint32_t &c : at) {
+            const uint32_t here = c;
+            c = sum;
+            sum += here;
+        }
+        for (uint64_t v : out)
+            tmp[at[static_cast<uint32_t>(v >> (32 + shift)) & kMask]++] = v;
+        out.swap(tmp);
+    }
+}
+
+// Puts pairs [first, first + m) of a call into a launch's inline ids.  src
+// null (a staging source): the pair's place in the call takes its place;
+// dst null (a staging destination): none.
+inline void inline_ids(uint32_t *ids, int mode, const int32_t *src, const int32_t *dst,
+                       const std::vector<uint64_t> &sorted, int64_t first, uint32_t m)
+{
+    for (uint32_t k = 0; k < m; ++k) {
+        const int64_t j = first + k;
+        uint32_t s, d;
+        if (!sorted.empty()) {
+            s = static_cast<uint32_t>(sorted[static_cast<size_t>(j)]);
+            d = static_cast<uint32_t>(sorted[static_cast<size_t>(j)] >> 32);
+        } else {
+            s = static_cast<uint32_t>(src ? src[j] : static_cast<int32_t>(j));
+            d = dst ? static_cast<uint32_t>(dst[j]) : 0u;
+        }
+        if (mode == kIds16) {
+            ids[k] = s | d << 16;
+        } else {
+            ids[k] = s;
+            ids[kInlinePairs + k] = d;
+        }
+    }
 }
 
 } // namespace

@@ -12,33 +12,41 @@
 // Kernel design (CDNA4, wave64):
 //  * In every layout a head's elements form one slab of block_size *
 //    head_dim * 2 bytes: contiguous in HND, HCNX and HDN, and block_size
-//    rows of head_dim * 2 bytes, one per token, in NHD.  A wavefront's work
-//    item is one (pair, layer, K/V, head) slab; it reads the slab with
-//    16-byte loads in the source's own order (whole rows, coalesced) and
-//    writes it with 16-byte stores in the destination's own order
-//    (contiguous), so neither side of HBM sees a partial row.
-//  * Between the two the slab passes through the wavefront's own LDS
-//    region, which is where the layouts transpose.  A 16-byte chunk is 8
-//    consecutive dims of one token in NHD, HND and HCNX, and 8 consecutive
-//    tokens of one dim in HDN.  Between the first three a chunk moves whole
-//    (one ds_read_b128 per chunk); to or from HDN every output chunk
-//    gathers 8 16-bit elements from 8 source chunks.  The LDS image has one
-//    16-byte pad after every 16 chunks, which spreads the strided reads of
-//    both cases over distinct banks for the common shapes (block_size 16,
-//    head_dim 64 or 128).
-//  * A plane whose two layouts agree (say K converts and V does not) moves
-//    chunk for chunk, registers straight to the store, without LDS.
-//  * Two wavefronts per workgroup (two adjacent heads of one tile).
-//    Measured on the LLaMA-7B stage: 8% faster than four when the source is
-//    token-major (its slabs are strided rows), equal the other way; one
-//    wavefront per workgroup, or several slabs per wavefront, did worse.
-//  * XCD-aware workgroup order: MI355X deals workgroups to its eight XCDs
-//    round robin, which scattered the sixteen workgroups of one tile over
-//    all eight.  Renumbered so that consecutive workgroups share an XCD,
-//    the token-major to head-major stage ran 1-9% faster (in-process, three
-//    processes), level with the same-layout copy; the copy itself gained
-//    nothing from the same change (1-2.5% slower), so it keeps the
-//    hardware's order.
+//    rows of head_dim * 2 bytes, one per token, in NHD.  A work item is one
+//    (pair, layer, K/V, head) slab; it is read with 16-byte loads in the
+//    source's own order (whole rows, coalesced) and written with 16-byte
+//    stores in the destination's own order (contiguous), so neither side of
+//    HBM sees a partial row.
+//  * convert_slabs, every uncapped launch: one workgroup per slab, one
+//    16-byte chunk per lane.  As in the same-layout copy, what bounds it is
+//    HBM and the DRAM order of the bytes in flight, so each wavefront moves
+//    1 KiB and the slabs run plane by plane over pairs sorted by destination
+//    block.  Against the kernel below (a slab per wavefront, 4 chunks a lane,
+//    pair by pair) on MI355X: 32 heads of 16 x 128, token-major to head-major
+//    6.33 -> 6.75 TB/s, to HCNX/HDN 6.28 -> 6.31, back 6.04 -> 6.59; 8 heads
+//    4.95 -> 6.49, 4.93 -> 6.15, 4.94 -> 6.30; one head 4.67 -> 6.06,
+//    4.64 -> 5.63, 4.63 -> 5.78.
+//  * Each XCD takes runs of kSlabRun = 64 slabs, so that the slabs of one
+//    token-major tile, which share its rows, meet in one L2.  32 heads,
+//    token-major to head-major: dealt in turn 6.12, runs of 16 6.56, 64
+//    6.75, 256 6.68, 1024 6.70 TB/s; 8 heads 6.12, 6.14, 6.49, 6.24, 6.38.
+//  * Between reading and writing the slab passes through LDS, which is where
+//    the layouts transpose.  A 16-byte chunk is 8 consecutive dims of one
+//    token in NHD, HND and HCNX, and 8 consecutive tokens of one dim in HDN.
+//    Between the first three a chunk moves whole (one ds_read_b128 per
+//    chunk); to or from HDN every output chunk gathers 8 16-bit elements
+//    from 8 source chunks.  The LDS image has one 16-byte pad after every 16
+//    chunks, which spreads the strided reads of both cases over distinct
+//    banks for the common shapes (block_size 16, head_dim 64 or 128).
+//  * A plane whose two layouts agree (say K converts and V does not), and
+//    one between NHD and HND (whose slabs hold their chunks in one order),
+//    moves chunk for chunk, registers straight to the store, without LDS.
+//  * convert_tiles, launches under a workgroup cap (the throttle of a
+//    migration's non-final stages): few resident workgroups, so each
+//    wavefront keeps a whole slab in flight.  Two wavefronts per workgroup
+//    (two adjacent heads of one tile): 8% faster than four when the source
+//    is token-major, equal the other way.  Consecutive workgroups share an
+//    XCD.
 //  * Index arithmetic divides chunk numbers (< 2^16) by per-call constants
 //    with a multiply-high by ceil(2^32 / divisor), exact in that range.
 //  * Block ids, layouts and base addresses are wavefront-uniform and come
@@ -53,6 +61,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <vector>
 
 #include "common.h"
 
@@ -61,6 +70,7 @@ namespace {
 constexpr int kMaxSlabChunksPerLane = 16;           // slabs of up to 16 KiB
 constexpr int kConvertWaves = 2;                    // wavefronts per workgroup
 constexpr uint32_t kXcds = 8;                       // accelerator dies the dispatcher deals workgroups to
+constexpr uint32_t kSlabRun = 64;                   // convert_slabs: slabs in a row on one XCD
 
 struct ConvertArgs {
     const uint64_t *src_tab;
@@ -78,7 +88,9 @@ struct ConvertArgs {
     uint32_t row_chunks;        // head_dim / 8: chunks of one token's head
     uint32_t t_chunks;          // block_size / 8: chunks of one dim's tokens (HDN)
     uint32_t chunks;            // chunks of one head slab
-    uint32_t units;             // wave items: pairs * 2 * num_layers * heads
+    uint32_t pairs;             // pairs in this launch
+    uint32_t units;             // slabs: pairs * 2 * num_layers * heads
+    uint32_t first_unit;        // this launch's first slab (convert_slabs)
     uint32_t lin_first;         // this launch's first pair within the whole call
     uint32_t lin_pairs;         // pairs in the whole call (plane stride of the staging buffer)
     int32_t layouts[4];         // source K, source V, destination K, destination V
@@ -136,6 +148,93 @@ __device__ __forceinline__ uint32_t convert_dst_id(const ConvertArgs &a, uint32_
     return IDS == kIds32 ? a.ids[kInlinePairs + i] : static_cast<uint32_t>(id_entry(a.dst_ids_dev, i));
 }
 
+// Output chunk k of a slab, gathered from the slab's padded LDS image (in the
+// source's chunk order).
+__device__ __forceinline__ u32x4 gather_chunk(const u32x4 *slab, uint32_t k, int32_t sl, int32_t dl,
+                                              const ConvertArgs &a)
+{
+    const uint16_t *slab16 = reinterpret_cast<const uint16_t *>(slab);
+    if (dl == LLMIG_LAYOUT_HDN) {
+        // tokens [8 tg, 8 tg + 8) of dim dd
+        const uint32_t dd = div_magic(k, a.magic_t);
+        const uint32_t tg = k - dd * a.t_chunks;
+        const uint32_t c = dd >> 3, e = dd & 7u;
+        uint32_t x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            x[j] = slab16[padded(dim_chunk_index(sl, 8u * tg + j, c, a)) * 8u + e];
+        return u32x4{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16)};
+    }
+    // dims [8 c, 8 c + 8) of token t
+    uint32_t t, c;
+    if (dl == LLMIG_LAYOUT_HCNX) {
+        c = div_magic(k, a.magic_bs);
+        t = k - c * a.block_size;
+    } else {
+        t = div_magic(k, a.magic_row);
+        c = k - t * a.row_chunks;
+    }
+    if (sl == LLMIG_LAYOUT_HDN) {
+        const uint32_t tg = t >> 3, e = t & 7u;
+        uint32_t x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            x[j] = slab16[padded((8u * c + j) * a.t_chunks + tg) * 8u + e];
+        return u32x4{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16)};
+    }
+    return slab[padded(dim_chunk_index(sl, t, c, a))];
+}
+
+// One workgroup per slab, one 16-byte chunk per lane (WAVES wavefronts cover
+// the slab; the launch leaves out those past its end).
+template <int IDS, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64) convert_slabs(const ConvertArgs a)
+{
+    __shared__ u32x4 lds[68 * WAVES];                // 64 WAVES chunks + one pad per 16
+    const uint32_t k = threadIdx.x;
+    uint32_t w = blockIdx.x;
+    // the dispatcher hands workgroup g to XCD g % 8: renumbered so that each
+    // XCD takes kSlabRun consecutive slabs (the grid's tail keeps its order)
+    const uint32_t round = w / (kXcds * kSlabRun), r8 = w % (kXcds * kSlabRun);
+    if ((round + 1u) * (kXcds * kSlabRun) <= gridDim.x)
+        w = round * (kXcds * kSlabRun) + (r8 % kXcds) * kSlabRun + r8 / kXcds;
+    const uint32_t unit = a.first_unit + w;
+    const uint32_t tile = unit / a.heads;
+    const uint32_t h = unit - tile * a.heads;
+    const uint32_t plane = tile / a.pairs;
+    const uint32_t i = tile - plane * a.pairs;
+    const uint32_t layer = plane >> 1, kv = plane & 1u;
+    const int32_t sl = a.layouts[kv], dl = a.layouts[2 + kv];
+
+    const uint8_t *s;
+    if (a.src_lin) {
+        const uint32_t x = IDS == kIdsDevice ? a.lin_first + i : uniform(convert_src_id<IDS>(a, i));
+        s = a.src_lin + (static_cast<uint64_t>(plane) * a.lin_pairs + x) * a.tile_bytes;
+    } else {
+        s = reinterpret_cast<const uint8_t *>(table_entry(a.src_tab, kv * a.num_layers + layer)) +
+            static_cast<uint64_t>(uniform(convert_src_id<IDS>(a, i))) * a.tile_bytes;
+    }
+    uint8_t *d = reinterpret_cast<uint8_t *>(table_entry(a.dst_tab, kv * a.num_layers + layer)) +
+                 static_cast<uint64_t>(uniform(convert_dst_id<IDS>(a, i))) * a.tile_bytes;
+    // lanes past the slab: out of the resource's range, loads 0 and stores nothing
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(s, a.tile_bytes);
+    const __amdgpu_buffer_rsrc_t rd = tile_rsrc(d, a.tile_bytes);
+    const bool in = k < a.chunks;
+    const u32x4 r = buffer_load16(rs, in ? slab_offset(sl, h, k, a) : kOutOfRange);
+    const uint32_t to = in ? slab_offset(dl, h, k, a) : kOutOfRange;
+    // NHD and HND hold a slab's chunks in one order (token by token): only
+    // the place of its rows in the tile differs
+    if (sl == dl || (sl <= LLMIG_LAYOUT_HND && dl <= LLMIG_LAYOUT_HND)) {
+        buffer_store16(rd, to, r);
+        return;
+    }
+    lds[padded(k)] = r;
+    __syncthreads();
+    if (in)
+        buffer_store16(rd, to, gather_chunk(lds, k, sl, dl, a));
+}
+
+// A capped grid: kConvertWaves wavefronts walk the slabs, N chunks per lane.
 template <int IDS, int N>
 __global__ void __launch_bounds__(kConvertWaves * 64) convert_tiles(const ConvertArgs a)
 {
@@ -143,14 +242,11 @@ __global__ void __launch_bounds__(kConvertWaves * 64) convert_tiles(const Conver
     const uint32_t lane = threadIdx.x % 64;
     const uint32_t wave = threadIdx.x / 64;
     u32x4 *mine = lds[wave];
-    const uint16_t *mine16 = reinterpret_cast<const uint16_t *>(mine);
     const uint32_t waves = gridDim.x * kConvertWaves;
     const uint32_t per_pair_plane = a.heads;
     const uint32_t planes = 2u * a.num_layers;
 
-    // XCD-aware order: the hardware hands workgroup g to XCD g % 8, so the
-    // logical workgroups are renumbered to put consecutive ones (the heads
-    // of one tile) on one XCD.
+    // consecutive workgroups (the heads of one tile) on one XCD
     const uint32_t full = gridDim.x - gridDim.x % kXcds;
     const uint32_t group = blockIdx.x < full ? (blockIdx.x % kXcds) * (full / kXcds) + blockIdx.x / kXcds
                                              : blockIdx.x;
@@ -164,12 +260,8 @@ __global__ void __launch_bounds__(kConvertWaves * 64) convert_tiles(const Conver
         const int32_t sl = a.layouts[kv], dl = a.layouts[2 + kv];
 
         const uint8_t *s;
-        if (a.src_lin) {
-            s = a.src_lin + (static_cast<uint64_t>(plane) * a.lin_pairs + a.lin_first + i) * a.tile_bytes;
-        } else {
-            s = reinterpret_cast<const uint8_t *>(table_entry(a.src_tab, kv * a.num_layers + layer)) +
-                static_cast<uint64_t>(uniform(convert_src_id<IDS>(a, i))) * a.tile_bytes;
-        }
+        s = reinterpret_cast<const uint8_t *>(table_entry(a.src_tab, kv * a.num_layers + layer)) +
+            static_cast<uint64_t>(uniform(convert_src_id<IDS>(a, i))) * a.tile_bytes;
         uint8_t *d = reinterpret_cast<uint8_t *>(table_entry(a.dst_tab, kv * a.num_layers + layer)) +
                      static_cast<uint64_t>(uniform(convert_dst_id<IDS>(a, i))) * a.tile_bytes;
         const __amdgpu_buffer_rsrc_t rs = tile_rsrc(s, a.tile_bytes);
@@ -206,40 +298,7 @@ __global__ void __launch_bounds__(kConvertWaves * 64) convert_tiles(const Conver
             const uint32_t k = lane + 64u * u;
             if (k >= a.chunks)
                 continue;
-            u32x4 v;
-            if (dl == LLMIG_LAYOUT_HDN) {
-                // Output chunk: tokens [8 tg, 8 tg + 8) of dim dd.
-                const uint32_t dd = div_magic(k, a.magic_t);
-                const uint32_t tg = k - dd * a.t_chunks;
-                const uint32_t c = dd >> 3, e = dd & 7u;
-                uint32_t x[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    x[j] = mine16[padded(dim_chunk_index(sl, 8u * tg + j, c, a)) * 8u + e];
-                v = u32x4{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16)};
-            } else {
-                // Output chunk: dims [8 c, 8 c + 8) of token t.
-                uint32_t t, c;
-                if (dl == LLMIG_LAYOUT_HCNX) {
-                    c = div_magic(k, a.magic_bs);
-                    t = k - c * a.block_size;
-                } else {
-                    t = div_magic(k, a.magic_row);
-                    c = k - t * a.row_chunks;
-                }
-                if (sl == LLMIG_LAYOUT_HDN) {
-                    const uint32_t tg = t >> 3, e = t & 7u;
-                    uint32_t x[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        x[j] = mine16[padded((8u * c + j) * a.t_chunks + tg) * 8u + e];
-                    v = u32x4{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16),
-                              x[6] | (x[7] << 16)};
-                } else {
-                    v = mine[padded(dim_chunk_index(sl, t, c, a))];
-                }
-            }
-            buffer_store16(rd, slab_offset(dl, h, k, a), v);
+            buffer_store16(rd, slab_offset(dl, h, k, a), gather_chunk(mine, k, sl, dl, a));
         }
         wave_lds_sync();
     }
@@ -262,11 +321,30 @@ const void *convert_kernel_n(int n)
     }
 }
 
-const void *convert_kernel(int ids, int n)
+template <int IDS>
+const void *convert_kernel_waves(int waves)
 {
+    switch (waves) {
+    case 16:
+        return reinterpret_cast<const void *>(&convert_slabs<IDS, 16>);
+    case 8:
+        return reinterpret_cast<const void *>(&convert_slabs<IDS, 8>);
+    case 4:
+        return reinterpret_cast<const void *>(&convert_slabs<IDS, 4>);
+    case 2:
+        return reinterpret_cast<const void *>(&convert_slabs<IDS, 2>);
+    default:
+        return reinterpret_cast<const void *>(&convert_slabs<IDS, 1>);
+    }
+}
+
+const void *convert_kernel(int ids, int n, bool capped)
+{
+    if (capped)
+        return ids == kIds16 ? convert_kernel_n<kIds16>(n) : convert_kernel_n<kIds32>(n);
     if (ids == kIdsDevice)
-        return convert_kernel_n<kIdsDevice>(n);
-    return ids == kIds16 ? convert_kernel_n<kIds16>(n) : convert_kernel_n<kIds32>(n);
+        return convert_kernel_waves<kIdsDevice>(n);
+    return ids == kIds16 ? convert_kernel_waves<kIds16>(n) : convert_kernel_waves<kIds32>(n);
 }
 
 uint64_t magic_for(uint32_t divisor)
@@ -288,12 +366,14 @@ int convert_chunks_per_lane(uint32_t chunks)
 // that the geometry is supported (16-bit elements, head_dim % 8 == 0,
 // block_size % 8 == 0 when a side is HDN, slabs of at most 16 KiB).
 // ids16: every id of both lists is below 65536 (pool to pool only).
+// max_workgroups > 0 (pool to pool with host ids only) caps the grid.
 int launch_convert(ConvertArgs a, const int32_t *src_ids, const int32_t *dst_ids, int64_t n, bool ids_on_device,
                    hipStream_t stream, uint32_t max_workgroups, const LaunchEvents &ev = LaunchEvents(),
                    bool ids16 = false)
 {
     const int ids = ids_on_device ? kIdsDevice : (src_ids && ids16) ? kIds16 : kIds32;
     const uint64_t inline_pairs = ids == kIds16 ? 2 * kInlinePairs : kInlinePairs;
+    const bool capped = max_workgroups > 0 && src_ids && !ids_on_device;
     const int per_lane = convert_chunks_per_lane(a.chunks);
     if (per_lane > kMaxSlabChunksPerLane)
         return LLMIG_EINVAL;
@@ -305,31 +385,45 @@ int launch_convert(ConvertArgs a, const int32_t *src_ids, const int32_t *dst_ids
                                                    ids_on_device ? UINT64_MAX : inline_pairs);
     if (per_launch == 0)
         return LLMIG_EINVAL;
-    const void *fn = convert_kernel(ids, per_lane);
+    std::vector<uint64_t> sorted;
+    if (!capped && !ids_on_device && n >= kSortPairs) {
+        try {
+            sort_pairs(src_ids, dst_ids, n, sorted);
+        } catch (...) {
+            sorted.clear();     // no memory for it: the caller's order
+        }
+    }
+    const void *fn = convert_kernel(ids, per_lane, capped);
+    const uint32_t threads = capped ? kConvertWaves * 64u : (a.chunks + 63u) / 64u * 64u;
+    // work-items of a launch are counted in 32 bits
+    const uint32_t step = capped ? 0x7fffffffu : (1u << 30) / threads;
     a.lin_pairs = static_cast<uint32_t>(n);
-    const int64_t launches = (n + static_cast<int64_t>(per_launch) - 1) / static_cast<int64_t>(per_launch);
-    for (int64_t first = 0, k = 0; first < n; first += static_cast<int64_t>(per_launch), ++k) {
+    int64_t launch = 0;
+    for (int64_t first = 0; first < n; first += static_cast<int64_t>(per_launch)) {
         const uint32_t m = static_cast<uint32_t>(std::min<int64_t>(n - first, per_launch));
+        a.pairs = m;
         a.units = static_cast<uint32_t>(m * units_per_pair);
         a.lin_first = static_cast<uint32_t>(first);
         if (ids == kIdsDevice) {
             a.src_ids_dev = src_ids ? src_ids + first : nullptr;
             a.dst_ids_dev = dst_ids + first;
-        } else if (ids == kIds16) {
-            for (uint32_t k = 0; k < m; ++k)
-                a.ids[k] = static_cast<uint32_t>(src_ids[first + k]) | (static_cast<uint32_t>(dst_ids[first + k]) << 16);
         } else {
-            if (src_ids)
-                std::memcpy(a.ids, src_ids + first, m * sizeof(int32_t));
-            std::memcpy(a.ids + kInlinePairs, dst_ids + first, m * sizeof(int32_t));
+            inline_ids(a.ids, ids, src_ids, dst_ids, sorted, first, m);
         }
         void *args[] = {&a};
-        uint32_t grid = std::min((a.units + kConvertWaves - 1) / kConvertWaves, kMaxGridWorkgroups);
-        if (max_workgroups > 0)
-            grid = std::min(grid, max_workgroups);
-        hipError_t e = launch_kernel(fn, dim3(grid), dim3(kConvertWaves * 64), args, stream, ev, k, launches);
-        if (e != hipSuccess)
-            return hip_error(e);
+        const bool last_pairs = first + static_cast<int64_t>(per_launch) >= n;
+        for (uint32_t at = 0; at < a.units; at += std::min(step, a.units - at)) {
+            const uint32_t here = std::min(step, a.units - at);
+            a.first_unit = at;
+            const uint32_t grid = capped ? std::min({(here + kConvertWaves - 1) / kConvertWaves, kMaxGridWorkgroups,
+                                                     max_workgroups})
+                                         : here;
+            const bool last = last_pairs && at + here == a.units;
+            hipError_t e = launch_kernel(fn, dim3(grid), dim3(threads), args, stream, ev, launch, last ? launch + 1 : -1);
+            if (e != hipSuccess)
+                return hip_error(e);
+            ++launch;
+        }
     }
     return LLMIG_OK;
 }

@@ -80,7 +80,6 @@
 #pragma once
 
 #include <algorithm>
-#include <cstring>
 #include <vector>
 
 #include "common.h"
@@ -119,13 +118,8 @@ struct CopyArgs {
 constexpr uint32_t kWaveRow = 64 * 16;         // one wavefront load: 1 KiB
 
 // Buffer offset of the row starting at byte o of a tile of `bytes` bytes:
-// o itself, or kOutOfRange when the row lies past the tile.  Tiles are at
-// most 2^31 - 1 bytes, so kOutOfRange plus a lane's offset is always past
-// the resource's range: the load returns zeros and the store is dropped.
-// A row that is partly inside the tile (a tile that is not a whole number
+// o itself, or kOutOfRange when the row lies past the tile.  A row that is partly inside the tile (a tile that is not a whole number
 // of KiB) is cut per lane by the same check.
-constexpr uint32_t kOutOfRange = 0x80000000u;
-
 __device__ __forceinline__ uint32_t row_offset(uint32_t o, uint32_t bytes)
 {
     return o < bytes ? o : kOutOfRange;
@@ -295,66 +289,6 @@ constexpr uint32_t kWavesPerCU = 32;
 constexpr uint32_t kBulkWaveItemsPerCU = 16;
 // Rows per launch: 64 lanes each, in 32-bit work-item counts.
 constexpr uint32_t kMaxRowsPerLaunch = 1u << 24;
-// Calls of fewer pairs keep the caller's order (too few to be neighbours).
-constexpr int64_t kSortPairs = 32;
-
-// Sorts the pairs of a call by destination id: out[k] = (source, destination)
-// as one word, source in the low half.  src null: the source of pair k is k.
-// A least-significant-digit radix sort, 11 bits a pass (two passes for 16-bit
-// ids), which leaves 512 pairs sorted in 2-3 us.
-void sort_pairs(const int32_t *src, const int32_t *dst, int64_t n, std::vector<uint64_t> &out)
-{
-    constexpr int kBits = 11;
-    constexpr uint32_t kMask = (1u << kBits) - 1;
-    std::vector<uint64_t> tmp(static_cast<size_t>(n));
-    out.resize(static_cast<size_t>(n));
-    uint32_t hi = 0;
-    for (int64_t k = 0; k < n; ++k) {
-        hi |= static_cast<uint32_t>(dst[k]);
-        out[static_cast<size_t>(k)] = static_cast<uint64_t>(static_cast<uint32_t>(dst[k])) << 32 |
-                                      static_cast<uint32_t>(src ? src[k] : static_cast<int32_t>(k));
-    }
-    for (int shift = 0; shift < 32 && (hi >> shift) != 0; shift += kBits) {
-        uint32_t at[kMask + 1] = {};
-        for (uint64_t v : out)
-            ++at[static_cast<uint32_t>(v >> (32 + shift)) & kMask];
-        uint32_t sum = 0;
-        for (uint32_t &c : at) {
-            const uint32_t here = c;
-            c = sum;
-            sum += here;
-        }
-        for (uint64_t v : out)
-            tmp[at[static_cast<uint32_t>(v >> (32 + shift)) & kMask]++] = v;
-        out.swap(tmp);
-    }
-}
-
-// Puts pairs [first, first + m) of a call into a launch's inline ids.  src
-// null (a staging source): the pair's place in the call takes its place;
-// dst null (a staging destination): none.
-inline void inline_ids(uint32_t *ids, int mode, const int32_t *src, const int32_t *dst,
-                       const std::vector<uint64_t> &sorted, int64_t first, uint32_t m)
-{
-    for (uint32_t k = 0; k < m; ++k) {
-        const int64_t j = first + k;
-        uint32_t s, d;
-        if (!sorted.empty()) {
-            s = static_cast<uint32_t>(sorted[static_cast<size_t>(j)]);
-            d = static_cast<uint32_t>(sorted[static_cast<size_t>(j)] >> 32);
-        } else {
-            s = static_cast<uint32_t>(src ? src[j] : static_cast<int32_t>(j));
-            d = dst ? static_cast<uint32_t>(dst[j]) : 0u;
-        }
-        if (mode == kIds16) {
-            ids[k] = s | d << 16;
-        } else {
-            ids[k] = s;
-            ids[kInlinePairs + k] = d;
-        }
-    }
-}
-
 // max_workgroups > 0 caps the grid (pool to pool with host ids only): fewer,
 // resident workgroups walk the items, leaving the rest of the chip (and of
 // HBM) to other work.  ids16: every id of both lists is below 65536 (pool to

@@ -79,3 +79,40 @@ def test_copy_rows(case, dev):
     torch.cuda.synchronize()
     orc.unpack(hd, into, want)
     assert image(dst).equals(hd), "unpack differs"
+
+
+# converting stages of more than one round of XCD runs, sorted pairs, slabs of
+# 1 to 16 wavefronts: layers, blocks, block_size, heads, head_dim, pairs
+CONVERT_CASES = [
+    (1, 60, 8, 3, 64, 50),          # 1 KiB slabs
+    (2, 80, 16, 5, 40, 70),         # 80 chunks: a partial second wavefront
+    (1, 40, 16, 13, 128, 33),       # 858 slabs: one round of runs and a tail
+    (1, 40, 32, 9, 128, 31),        # 8 KiB slabs, too few pairs to sort
+    (1, 34, 64, 2, 128, 34),        # 16 KiB slabs
+    (1, 600, 8, 2, 16, 530),        # 256-byte slabs, two launches
+]
+
+
+@pytest.mark.parametrize("dev", [False, True], ids=["host", "device"])
+@pytest.mark.parametrize("case", CONVERT_CASES, ids=lambda c: f"slab{c[2] * c[4] * 2}_n{c[5]}")
+def test_convert_slabs(case, dev):
+    print("[case]", case, dev, flush=True)
+    layers, blocks, bs, heads, dim, n = case
+    shape = wl.PoolShape(layers, blocks, bs, heads, dim, "fp16")
+    orc = oracle.default()
+    for sl, dl in (((0, 0), (1, 1)), ((0, 1), (2, 3)), ((2, 3), (0, 0)), ((3, 2), (1, 1)), ((1, 0), (1, 3))):
+        src, dst = pool(shape, 80 + n, wl.SRC_VALUES), pool(shape, 80 + n, wl.DST_VALUES)
+        src = Pool(src.k, src.v, sl)
+        dst = Pool(dst.k, dst.v, dl)
+        g = wl.stream(80 + n, wl.EXTRA)
+        ms, md, into = (g.choice(blocks, n, replace=False).astype(np.int32) for _ in range(3))
+        hs, hd = image(src), image(dst)
+        llmig.llmig_stage(src, dst, where(ms, dev), where(md, dev))
+        torch.cuda.synchronize()
+        orc.copy_layout(hs, sl, hd, dl, ms, md, heads, dim, 2)
+        assert image(dst).equals(hd) and image(src).equals(hs), f"stage {sl} -> {dl} differs from the oracle"
+        packed = orc.pack(hs, ms)
+        llmig.llmig_unpack_layout(dst, where(into, dev), torch.from_numpy(packed).cuda(), sl)
+        torch.cuda.synchronize()
+        orc.unpack_layout(hd, dl, into, packed, sl, heads, dim, 2)
+        assert image(dst).equals(hd), f"converting unpack {sl} -> {dl} differs"
