@@ -369,9 +369,11 @@ int llmig_stream_read(const void *region, int64_t bytes, int32_t passes, int32_t
  * fp16, 1 bf16), 16-byte aligned; tables device int32, ids the caller
  * guarantees in range; ctx_lens a HOST array; out device float32
  * [num_layers][batch][q_heads][head_dim], 16-byte aligned; a sequence of
- * length 0 gives zeros.  workspace: device memory of at least the size
+ * length 0 gives zeros.  workspace: device memory of the size
  * llmig_decode_attention_workspace returns for the same lengths, 16-byte
- * aligned.
+ * aligned.  (That size lets a small call be cut finely enough to use the
+ * whole chip.  A call also takes any size that holds, per layer and query
+ * head, head_dim + 4 floats for each 2048 tokens begun of every sequence.)
  * Supported: NHD pools, head_dim 64 or 128, q_heads / num_kv_heads in
  * {1, 2, 4, 8, 16}, batch <= 256; else LLMIG_EINVAL.  Arithmetic in fp32. */
 int llmig_decode_attention_workspace(const int32_t *ctx_lens, int32_t batch, int32_t num_layers,

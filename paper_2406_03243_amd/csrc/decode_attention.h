@@ -7,14 +7,18 @@
 // over the sequence's ctx tokens, reached through its block table; inputs
 // are fp16 or bf16, accumulation and output fp32.
 //
-// Layout of the work: sequences are cut into partitions of kPartTokens
-// tokens (flash-decoding), so a long request does not leave one workgroup
-// working alone; a workgroup takes one (layer, partition, KV head) and its
-// four wavefronts take alternate 16-token groups of the partition; a second
-// kernel merges the partitions of each sequence.  With `group` query heads
-// per KV head, every K/V byte feeds `group` multiply-adds, a small dense
-// contraction that runs on the matrix cores (see attn_partial_mfma).
+// Layout of the work: sequences are cut into partitions of at most
+// kPartTokens tokens (flash-decoding), so a long request does not leave one
+// workgroup working alone; a workgroup takes one (partition, layer, KV head)
+// and its four wavefronts take alternate 16-token groups of the partition; a
+// second kernel merges the partitions of each sequence of more than one (a
+// sequence of one partition is finished by its workgroup).  With `group`
+// query heads per KV head, every K/V byte feeds `group` multiply-adds, a
+// small dense contraction that runs on the matrix cores (see
+// attn_partial_mfma).
 #pragma once
+
+#include <algorithm>
 
 #include "common.h"
 
@@ -28,27 +32,32 @@ namespace {
 constexpr int kWaitVm0 = 0x0F70;
 constexpr int kWaitLgkm0 = 0xC07F;
 
-constexpr int kPartTokens = 2048;    // tokens per partition
-constexpr int kAttnItems = 128;      // (sequence, partition) items per launch, in the kernel arguments
-constexpr int kAttnMaxBatch = 256;   // sequences per call (per-sequence item ranges ride in the arguments)
+constexpr int kPartTokens = 2048;    // most tokens per partition
+constexpr int kMinPartTokens = 128;  // fewest tokens a sequence is split down to
+constexpr int kAttnMaxBatch = 256;   // sequences per call (their partitions ride in the kernel arguments)
 // A partial result record: the partition's maximum score m (natural base),
 // its weight sum l, two floats of padding, then the D weighted V sums, so
 // that records (D + kAttnHeader floats) and their sums start on 16 bytes.
 constexpr int kAttnHeader = 4;
 
+// The sequences of a call in launch order: those cut into several partitions
+// first, then those of one partition, each longest partition first.  Items
+// (partitions) are numbered through that order, so the items that leave
+// partial results are 0 .. n_records - 1.
 struct AttnArgs {
     const uint64_t *k_tab;      // pool tables: K bases then V bases
     const uint8_t *q;           // [L][B][Hq][D]
     const int32_t *tables;      // [B][table_stride]
-    float *ws;                  // partial results: [L][n_items][Hq][D + kAttnHeader]
+    float *ws;                  // partial results: [L][n_records][Hq][D + kAttnHeader]
+    float *out;                 // [L][B][Hq][D]
     float scale;
     uint32_t num_layers, batch, q_heads, kv_heads, block_size, table_stride;
-    uint32_t item_base;         // global index of this launch's first item
-    uint32_t n_items_total;     // items of the whole call
-    uint32_t items;             // items in this launch
-    int32_t item_seq[kAttnItems];
-    int32_t item_start[kAttnItems];
-    int32_t item_end[kAttnItems];
+    uint32_t item_base;         // this launch's first item
+    uint32_t n_records;         // items that leave a partial result
+    uint32_t part_tokens;       // most tokens of a partition in this call
+    uint32_t item_end[kAttnMaxBatch];  // items of the first s + 1 sequences
+    int32_t ctx[kAttnMaxBatch];        // tokens of sequence s
+    uint8_t seq[kAttnMaxBatch];        // its number in the batch
     // The stage copy a migrating launch carries (read only when it does):
     // logical blocks [mig_from, mig_to) of sequence mig_seq go to the blocks
     // mig_ids[j - mig_from] of the pool whose K and V bases dst_tab lists.
@@ -62,66 +71,96 @@ struct AttnArgs {
 struct AttnReduceArgs {
     const float *ws;
     float *out;                 // [L][B][Hq][D]
-    uint32_t num_layers, batch, q_heads, head_dim, n_items_total;
-    int32_t seq_first[kAttnMaxBatch];   // first item of each sequence
-    int32_t seq_count[kAttnMaxBatch];   // its number of items (0 for an empty sequence)
+    uint32_t num_layers, batch, q_heads, head_dim, n_records;
+    uint64_t row_base;                  // this launch's first row
+    uint32_t seqs;                      // sequences of several partitions
+    uint32_t seq_end[kAttnMaxBatch];    // records of the first s + 1 of them
+    uint8_t seq[kAttnMaxBatch];         // their numbers in the batch
 };
 
-// One lane per (layer, sequence, query head, four dimensions): merges the
-// partitions of the sequence and normalises.  A lane reads each partition's
-// m and l as one 8-byte load and its four sums as one 16-byte load, eight
-// partitions at a time so their loads are in flight together; the
-// head_dim / 4 lanes of one (layer, sequence, query head) read one record's
-// sums whole.
+// Tokens per partition of a sequence of n tokens cut into `parts` partitions:
+// equal shares, whole rounds of the four wavefronts' 16-token groups.
+__host__ __device__ inline int32_t attn_part_len(int32_t n, uint32_t parts)
+{
+    const int64_t share = (static_cast<int64_t>(n) + parts - 1) / parts;
+    return static_cast<int32_t>((share + 63) / 64 * 64);
+}
+
+// Merges the partitions of each sequence and normalises.  A workgroup takes
+// one (layer, sequence, query head) row: its lanes are SUB groups of
+// head_dim / 4, each merging every SUB-th partition, eight partitions' loads
+// in flight (a record's m and l as one 8-byte load, four sums per lane as one
+// 16-byte load); the groups meet in LDS.  SUB = 1 packs several rows into a
+// workgroup, for calls of at most eight partitions a sequence.
+template <int D, int SUB>
 __global__ void __launch_bounds__(kThreads) attn_reduce(const AttnReduceArgs a)
 {
-    const uint32_t quads = a.head_dim / 4;
-    const uint32_t rec = a.head_dim + kAttnHeader;                       // floats per record
-    const uint64_t total = static_cast<uint64_t>(a.num_layers) * a.batch * a.q_heads * quads;
-    for (uint64_t x = static_cast<uint64_t>(blockIdx.x) * kThreads + threadIdx.x; x < total;
-         x += static_cast<uint64_t>(gridDim.x) * kThreads) {
-        const uint32_t d4 = x % quads;
-        uint64_t r = x / quads;
-        const uint32_t h = r % a.q_heads;
-        r /= a.q_heads;
-        const uint32_t b = r % a.batch;
-        const uint32_t layer = static_cast<uint32_t>(r / a.batch);
-        float m = -INFINITY, l = 0.f;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        const int32_t count = a.seq_count[b];
-        const uint64_t stride = static_cast<uint64_t>(a.q_heads) * rec;  // one partition
-        const float *base = a.ws + ((static_cast<uint64_t>(layer) * a.n_items_total + a.seq_first[b]) * a.q_heads + h) *
-                                       rec;
-        for (int32_t p0 = 0; p0 < count; p0 += 8) {
-            float2 ml[8];
-            float4 v[8];
+    constexpr uint32_t kQuads = D / 4, kRec = D + kAttnHeader;
+    constexpr uint32_t kRows = kThreads / (kQuads * SUB);     // rows per workgroup
+    static_assert(SUB == 1 || kRows == 1, "several groups: one row per workgroup");
+    const uint64_t rows = static_cast<uint64_t>(a.num_layers) * a.seqs * a.q_heads;
+    const uint32_t d4 = threadIdx.x % kQuads, sub = SUB > 1 ? threadIdx.x / kQuads : 0u;
+    uint64_t r = a.row_base + static_cast<uint64_t>(blockIdx.x) * kRows + (SUB > 1 ? 0u : threadIdx.x / kQuads);
+    const bool in = r < rows;
+    if (!in)
+        r = rows - 1;
+    const uint32_t h = r % a.q_heads;
+    const uint32_t s = (r / a.q_heads) % a.seqs;
+    const uint32_t layer = static_cast<uint32_t>(r / a.q_heads / a.seqs);
+    const uint32_t first = s > 0 ? a.seq_end[s - 1] : 0u;
+    const int32_t count = static_cast<int32_t>(a.seq_end[s] - first);
+    const uint64_t stride = static_cast<uint64_t>(a.q_heads) * kRec;  // one partition
+    const float *base = a.ws + ((static_cast<uint64_t>(layer) * a.n_records + first) * a.q_heads + h) * kRec;
+    float m = -INFINITY, l = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto merge = [&](float m2, float l2, float4 v) {
+        const float mm = fmaxf(m, m2);
+        if (mm == -INFINITY)
+            return;
+        const float c1 = __expf(m - mm), c2 = __expf(m2 - mm);
+        l = l * c1 + l2 * c2;
+        acc.x = acc.x * c1 + v.x * c2;
+        acc.y = acc.y * c1 + v.y * c2;
+        acc.z = acc.z * c1 + v.z * c2;
+        acc.w = acc.w * c1 + v.w * c2;
+        m = mm;
+    };
+    for (int32_t p0 = static_cast<int32_t>(sub); p0 < count; p0 += 8 * SUB) {
+        float2 ml[8];
+        float4 v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                ml[u] = make_float2(-INFINITY, 0.f);
-                v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (p0 + u < count) {
-                    const float *src = base + (p0 + u) * stride;
-                    ml[u] = *reinterpret_cast<const float2 *>(src);
-                    v[u] = *reinterpret_cast<const float4 *>(src + kAttnHeader + 4 * d4);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float mm = fmaxf(m, ml[u].x);
-                if (mm == -INFINITY)
-                    continue;
-                const float c1 = __expf(m - mm), c2 = __expf(ml[u].x - mm);
-                l = l * c1 + ml[u].y * c2;
-                acc.x = acc.x * c1 + v[u].x * c2;
-                acc.y = acc.y * c1 + v[u].y * c2;
-                acc.z = acc.z * c1 + v[u].z * c2;
-                acc.w = acc.w * c1 + v[u].w * c2;
-                m = mm;
+        for (int u = 0; u < 8; ++u) {
+            ml[u] = make_float2(-INFINITY, 0.f);
+            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (p0 + u * SUB < count) {
+                const float *src = base + (p0 + u * SUB) * stride;
+                ml[u] = *reinterpret_cast<const float2 *>(src);
+                v[u] = *reinterpret_cast<const float4 *>(src + kAttnHeader + 4 * d4);
             }
         }
-        reinterpret_cast<float4 *>(a.out)[x] =
-            l > 0.f ? make_float4(acc.x / l, acc.y / l, acc.z / l, acc.w / l) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            merge(ml[u].x, ml[u].y, v[u]);
     }
+    if constexpr (SUB > 1) {
+        __shared__ float sm[SUB], sl[SUB];
+        __shared__ float4 sv[SUB][kQuads];
+        sv[sub][d4] = acc;
+        if (d4 == 0) {
+            sm[sub] = m;
+            sl[sub] = l;
+        }
+        __syncthreads();
+        if (sub > 0)
+            return;
+#pragma unroll
+        for (int u = 1; u < SUB; ++u)
+            merge(sm[u], sl[u], sv[u][d4]);
+    }
+    if (in)
+        reinterpret_cast<float4 *>(a.out)[((static_cast<uint64_t>(layer) * a.batch + a.seq[s]) * a.q_heads + h) * kQuads +
+                                          d4] =
+            l > 0.f ? make_float4(acc.x / l, acc.y / l, acc.z / l, acc.w / l) : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // ---------------------------------------------------------------------------
@@ -141,27 +180,36 @@ __global__ void __launch_bounds__(kThreads) attn_reduce(const AttnReduceArgs a)
 //                     distinct banks;
 //   online softmax per query row (a lane's rows of S^T are the tokens
 //                     4*(lane/16) .. +3 of query row lane%16);
-//   O^T += V^T . P^T  16x16x16 MFMA per 16 dims; P^T is already in the
+//   O^T += V^T . P^T  16x16x32 MFMA per 16 dims; P^T is already in the
 //                     B-operand layout, and V^T comes out of the row-major V
 //                     rows through gfx950's transposing LDS read
 //                     (ds_read_b64_tr_b16).  P is split into a 16-bit high
-//                     part and the 16-bit rounding of the remainder, two
-//                     MFMAs, so the weights keep ~2^-16 (bf16) / 2^-22 (fp16)
-//                     precision.
+//                     part and the 16-bit rounding of the remainder, which
+//                     take the two halves of the contraction, so the weights
+//                     keep ~2^-16 (bf16) / 2^-22 (fp16) precision.
 // The four wavefronts take alternate token groups of the partition and merge
 // their states through LDS at the end.  The kernel waits on HBM, not on the
 // matrix cores or LDS, so it is built for four wavefronts per SIMD (at most
 // 128 registers: the accumulators move from AGPRs to VGPRs; 32 KiB of LDS
 // per workgroup for the rows).
-// Measured on MI355X, one process, alternating, on a GQA decode step (80
-// layers, 8 KV heads of 128, 17 sequences, 65,280 tokens), each step against
-// the kernel before it: whole-row K loads rearranged through LDS instead of
-// K fragments loaded straight into the operand layout (16 rows x 64 bytes
-// per load instruction) +8%; grouping each (layer, partition)'s KV heads on
-// one XCD +7%; 2048-token partitions instead of 1024 +4%; rows loaded
-// straight into LDS one group ahead instead of through registers, with the
-// transposing V^T reads, +2% (bit-identical output).  0.63 -> 0.77 of HBM
-// peak for the partial kernel.
+// What a workgroup spends besides its loop is what bounds short sequences:
+// each dependent access costs the latency of a loaded memory system (~5 us
+// with every CU's 128 KiB in flight).  So the block ids are one load per lane
+// (UNITS), partitions run longest first over all layers (the launch ends on
+// short ones), a sequence of one partition needs no record and no merge, and
+// results leave in whole rows at device scope.  Measured on MI355X against
+// partitions in batch order, layer by layer, ids staged behind a barrier,
+// every result through a record and the merge, scattered 64-byte stores: 32
+// layers of 32 heads, 8 sequences of 200-1500 tokens, 752 -> 505 us (4.34 ->
+// 6.46 TB/s); 64 of 40-300, 899 -> 789; 80 layers of 8 heads (64 query
+// heads), 16 of 550-4096, 1498 -> 1255 (5.03 -> 6.0 TB/s); 17 of 520-3840,
+// 1846 -> 1670; 32 layers of one sequence of 32000, 701 -> 676.
+// Earlier steps on the same kernel: whole-row K loads rearranged through LDS
+// instead of K fragments loaded straight into the operand layout (16 rows x
+// 64 bytes per load instruction) +8%; grouping each (partition, layer)'s KV
+// heads on one XCD +7%; 2048-token partitions instead of 1024 +4%; rows
+// loaded straight into LDS one group ahead instead of through registers, with
+// the transposing V^T reads, +2%.
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -179,16 +227,20 @@ __device__ __forceinline__ f32x4_t mfma_qk(u32x4 a, u32x4 b, f32x4_t c)
                                                        __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
 }
 
+// The high and the low part of the weights in one 16x16x32 product: k slots
+// 8*g4 .. +3 hold the weights' high parts of tokens 4*g4 .. +3, slots + 4 .. 7
+// their low parts, against the same V rows twice.
 template <int BF16>
-__device__ __forceinline__ f32x4_t mfma_pv(uint64_t a, uint64_t b, f32x4_t c)
+__device__ __forceinline__ f32x4_t mfma_pv(uint64_t v, uint64_t hi, uint64_t lo, f32x4_t c)
 {
-    if constexpr (BF16)
-        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4_t, a),
-                                                          __builtin_bit_cast(i16x4_t, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, a),
-                                                      __builtin_bit_cast(f16x4_t, b), c, 0, 0, 0);
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    return mfma_qk<BF16>(__builtin_bit_cast(u32x4, u64x2{v, v}), __builtin_bit_cast(u32x4, u64x2{hi, lo}), c);
 }
+
+// Results leave at device scope (sc1).  On a step whose rows come out of the
+// caches (32 layers, 8 KV heads of 8 query heads, 32 sequences of 1000
+// tokens) sc1 stores 602 us, nt 612, plain ones 679, no stores at all 533.
+constexpr int kResultStore = 16;
 
 // Round a float to the 16-bit type (nearest even); returns the bits.
 template <int BF16>
@@ -202,14 +254,13 @@ __device__ __forceinline__ uint32_t to16(float x)
     }
 }
 
-// Block ids a partition can touch, for the dynamic LDS of attn_partial_mfma:
-// a partition starts on a block boundary (kPartTokens is a multiple of every
-// block size that divides it) or inside a block, so at most
-// ceil(kPartTokens / block_size) + 1 blocks.  A migrating launch keeps the
+// Block ids a partition can touch, for the dynamic LDS of attn_partial_mfma
+// (UNITS 0): a partition may start inside a block, so at most
+// ceil(part_tokens / block_size) + 1 blocks.  A migrating launch keeps the
 // destination id of each of them beside it.
-__host__ __device__ inline uint32_t attn_blk_slots(uint32_t block_size)
+__host__ __device__ inline uint32_t attn_blk_slots(uint32_t part_tokens, uint32_t block_size)
 {
-    return (kPartTokens + block_size - 1) / block_size + 1;
+    return (part_tokens + block_size - 1) / block_size + 1;
 }
 
 // MIG: the launch also carries a migration stage of one sequence (Llumnix
@@ -223,7 +274,14 @@ __host__ __device__ inline uint32_t attn_blk_slots(uint32_t block_size)
 // would write, while HBM reads them once, for the attention (of the
 // sequence's partly filled last block, which only a final stage includes,
 // the rows of its tokens: the slots past them hold no token).
-template <int BF16, int D, int MIG>
+//
+// UNITS: block_size is a multiple of 8, so every 8-token unit of a group
+// (partitions start on multiples of 64 tokens) lies in one block: lane l of a
+// wavefront looks up the row of its l-th unit once, and a request takes the
+// rows of a unit from one lane (v_readlane: a scalar base plus lane offsets
+// that never change).  A partition has at most 64 units per wavefront.  Other
+// block sizes stage the block ids in LDS and look each token's up.
+template <int BF16, int D, int MIG, int UNITS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
 attn_partial_mfma(const AttnArgs a)
 {
@@ -233,28 +291,33 @@ attn_partial_mfma(const AttnArgs a)
     constexpr int RPL = 64 / LPR;         // rows per load instruction
     constexpr int RB = D * 2;             // bytes of one K or V row
     constexpr int RPB = 128 / D;          // rows per 256 bytes (one pass over the 64 banks)
+    constexpr int IPU = KS / 2;           // load instructions per 8-token unit (K and V each)
     constexpr float kLog2e = 1.4426950408889634f;
     // 4 wavefronts x (16 K rows + 16 V rows) in the loop; reused for the
-    // final merge of 4 x D x 16 floats.
-    constexpr int kRowBytes = 4 * 2 * 16 * RB, kMergeBytes = 4 * D * 16 * 4;
+    // final merge of 4 x 16 rows of kMergeRow floats (four of padding).
+    constexpr int kMergeRow = D + 4;
+    constexpr int kRowBytes = 4 * 2 * 16 * RB, kMergeBytes = 4 * 16 * kMergeRow * 4;
     static_assert(KS * 64 * 16 == 16 * RB, "KS load instructions of 1 KiB cover the 16 rows of a group");
+    static_assert(IPU * RPL == 8, "IPU load instructions cover the 8 rows of a unit");
+    static_assert(kPartTokens <= 64 * 4 * 8, "a lane per unit of a wavefront's share of a partition");
     __shared__ __align__(16) uint8_t smem[kRowBytes > kMergeBytes ? kRowBytes : kMergeBytes];
     __shared__ float sh_m[4][16], sh_l[4][16];
-    // block ids of the partition: dynamic LDS of attn_blk_slots(block_size)
+    // UNITS 0: block ids of the partition, dynamic LDS of attn_blk_slots
     // entries (a migrating launch: twice that, the destination ids after them)
     extern __shared__ int32_t sh_blk[];
 
     // The dispatcher deals workgroups to the eight XCDs in turn.  Renumbered
-    // here so that the kv_heads workgroups of one (layer, item), which read
+    // here so that the kv_heads workgroups of one (item, layer), which read
     // adjacent 256-byte pieces of the same token rows, run one after another
     // on one XCD: linear workgroup w is the (w / 8)-th on XCD w % 8.  The
     // tail of the grid that does not fill whole rounds of 8 * kv_heads keeps
-    // the plain order.
+    // the plain order.  Items run longest first, all layers of one after the
+    // other, so the last workgroups to run are short ones.
     uint32_t item, g, layer;
     {
-        const uint32_t H = a.kv_heads, lin = blockIdx.x + blockIdx.y * gridDim.x;
-        const uint32_t total = gridDim.x * gridDim.y, full = total - total % (8u * H);
-        uint32_t unit;                    // (layer, item) in row-major order
+        const uint32_t H = a.kv_heads, lin = blockIdx.x;
+        const uint32_t full = gridDim.x - gridDim.x % (8u * H);
+        uint32_t unit;                    // (item, layer) in row-major order
         if (lin < full) {
             const uint32_t k = lin / 8u;
             g = k % H;
@@ -263,37 +326,75 @@ attn_partial_mfma(const AttnArgs a)
             g = lin % H;
             unit = lin / H;
         }
-        layer = unit / a.items;
-        item = unit - layer * a.items;
+        item = unit / a.num_layers;
+        layer = unit - item * a.num_layers;
+        item = uniform(item + a.item_base);
+        layer = uniform(layer);
     }
-    const uint32_t b = static_cast<uint32_t>(a.item_seq[item]);
-    const int32_t start = a.item_start[item], end = a.item_end[item];
+    // the item's sequence: the first one whose items end past it
+    uint32_t s_lo = 0, s_hi = a.batch - 1;
+    while (s_lo < s_hi) {
+        const uint32_t mid = (s_lo + s_hi) / 2u;
+        if (a.item_end[mid] <= item)
+            s_lo = mid + 1u;
+        else
+            s_hi = mid;
+    }
+    const uint32_t item_first = s_lo > 0 ? a.item_end[s_lo - 1] : 0u;
+    const uint32_t parts = a.item_end[s_lo] - item_first;
+    const uint32_t b = a.seq[s_lo];
+    const int32_t ctx = a.ctx[s_lo];
+    const int32_t plen = attn_part_len(ctx, parts);
+    const int32_t start = static_cast<int32_t>(item - item_first) * plen;
+    const int32_t end = min(ctx, start + plen);
     const uint32_t G = a.q_heads / a.kv_heads;
     const uint32_t wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const uint32_t wv = uniform(wave);
     const uint32_t r16 = lane % 16, g4 = lane / 16;
+    const int32_t bs = static_cast<int32_t>(a.block_size);
 
     const uint8_t *kbase = reinterpret_cast<const uint8_t *>(table_entry(a.k_tab, layer));
     const uint8_t *vbase = reinterpret_cast<const uint8_t *>(table_entry(a.k_tab, a.num_layers + layer));
 
-    // The partition's block ids, once, so no token waits on a table load.
-    const int32_t *table = a.tables + static_cast<uint64_t>(b) * a.table_stride;
-    const int32_t first_blk = start / static_cast<int32_t>(a.block_size);
-    const int32_t n_blk = (end - 1) / static_cast<int32_t>(a.block_size) - first_blk + 1;
-    for (int32_t k = threadIdx.x; k < n_blk; k += kThreads)
-        sh_blk[k] = table[first_blk + k];
     // A migrating launch: whether this workgroup's rows are the migrating
-    // sequence's, and the destination block of each of its logical blocks
-    // (-1 outside the stage).
+    // sequence's.
     const bool mig = MIG && static_cast<int32_t>(b) == a.mig_seq;
-    int32_t *sh_dst = sh_blk + attn_blk_slots(a.block_size);
-    if (mig) {
-        for (int32_t k = threadIdx.x; k < n_blk; k += kThreads) {
-            const int32_t j = first_blk + k;
-            const int32_t id = j >= a.mig_from && j < a.mig_to ? a.mig_ids[j - a.mig_from] : -1;
-            sh_dst[k] = id < a.dst_blocks ? id : -1;     // an id past the pool is not written
+    const int32_t *table = a.tables + static_cast<uint64_t>(b) * a.table_stride;
+    const int32_t tg0 = start + 16 * static_cast<int32_t>(wv);
+    const int32_t first_blk = UNITS ? 0 : start / bs;
+    int32_t *sh_dst = sh_blk + attn_blk_slots(a.part_tokens, a.block_size);
+    // UNITS: lane l's unit is tokens tg0 + 64 * (l / 2) + 8 * (l % 2) .. + 7:
+    // the slot (block * block_size + slot in it) of its first token, or, past
+    // the partition's end, of the partition's last token; and where the unit
+    // lands in the destination pool (-1: not in the stage).
+    uint32_t unit_slot = 0;
+    int32_t unit_dst = -1;
+    if constexpr (UNITS) {
+        if (tg0 < end) {
+            const int32_t t = min(tg0 + 64 * static_cast<int32_t>(lane / 2) + 8 * static_cast<int32_t>(lane % 2), end - 1);
+            const int32_t blk = t / bs;
+            unit_slot = static_cast<uint32_t>(table[blk]) * a.block_size + static_cast<uint32_t>(t - blk * bs);
+            if (mig && blk >= a.mig_from && blk < a.mig_to) {
+                const int32_t id = a.mig_ids[blk - a.mig_from];
+                if (id >= 0 && id < a.dst_blocks)      // an id outside the pool is not written
+                    unit_dst = id * bs + (t - blk * bs);
+            }
         }
+    } else {
+        // the partition's block ids, once, and the destination block of each
+        // of its logical blocks (-1 outside the stage)
+        const int32_t n_blk = end > start ? (end - 1) / bs - first_blk + 1 : 0;
+        for (int32_t k = threadIdx.x; k < n_blk; k += kThreads)
+            sh_blk[k] = table[first_blk + k];
+        if (mig) {
+            for (int32_t k = threadIdx.x; k < n_blk; k += kThreads) {
+                const int32_t j = first_blk + k;
+                const int32_t id = j >= a.mig_from && j < a.mig_to ? a.mig_ids[j - a.mig_from] : -1;
+                sh_dst[k] = id < a.dst_blocks ? id : -1;     // an id past the pool is not written
+            }
+        }
+        __syncthreads();
     }
-    __syncthreads();
 
     // Q^T fragments (B operand): query row r16 of the group, dims 32*ks + 8*g4 .. +8.
     u32x4 qf[KS];
@@ -317,7 +418,6 @@ attn_partial_mfma(const AttnArgs a)
     // bytes a row.  K chunk c of local token t sits at slot c ^ kswz(t), so
     // that the 16 tokens an operand read touches at once fall on distinct
     // banks; V rows are plain (the transposing reads take them as they are).
-    const uint32_t wv = __builtin_amdgcn_readfirstlane(wave);
     uint8_t *kbuf = smem + wv * (2 * 16 * RB);
     uint8_t *vbuf = kbuf + 16 * RB;
     auto kswz = [](uint32_t t) { return (t / RPB) % LPR; };
@@ -326,17 +426,41 @@ attn_partial_mfma(const AttnArgs a)
     // j*RPL + lane/LPR into LDS slot lane%LPR of that token's row.  A token
     // past the partition's end loads its last token; its score is masked
     // below, so its weight is 0.
+    const uint32_t lrow = lane / LPR, lslot = lane % LPR;
+    const uint32_t row_bytes = a.kv_heads * RB;             // one token's rows of every KV head
+    auto load_rows = [&](int j, const uint8_t *k, const uint8_t *v) {
+        __builtin_amdgcn_global_load_lds((const void LLMIG_GLOBAL *)k, (void LLMIG_LDS *)(kbuf + j * 1024), 16, 0,
+                                         kStreamLoad);
+        __builtin_amdgcn_global_load_lds((const void LLMIG_GLOBAL *)v, (void LLMIG_LDS *)(vbuf + j * 1024), 16, 0,
+                                         kStreamLoad);
+    };
     auto request_group = [&](int32_t t0) {
+        if constexpr (UNITS) {
+            const uint32_t u0 = static_cast<uint32_t>(t0 - tg0) / 32u;      // the group's first unit (lane)
 #pragma unroll
-        for (int j = 0; j < KS; ++j) {
-            const uint32_t tl = j * RPL + lane / LPR, slot = lane % LPR;
-            const int32_t t = min(t0 + static_cast<int32_t>(tl), end - 1);
-            const uint64_t row = (static_cast<uint64_t>(sh_blk[t / a.block_size - first_blk]) * a.block_size +
-                                  t % a.block_size) * a.kv_heads + g;
-            __builtin_amdgcn_global_load_lds((const void LLMIG_GLOBAL *)(kbase + (row * D + 8 * (slot ^ kswz(tl))) * 2),
-                                             (void LLMIG_LDS *)(kbuf + j * 1024), 16, 0, kStreamLoad);
-            __builtin_amdgcn_global_load_lds((const void LLMIG_GLOBAL *)(vbase + (row * D + 8 * slot) * 2),
-                                             (void LLMIG_LDS *)(vbuf + j * 1024), 16, 0, kStreamLoad);
+            for (int half = 0; half < 2; ++half) {
+                const uint32_t slot = __builtin_amdgcn_readlane(unit_slot, u0 + half);
+                const uint64_t base = (static_cast<uint64_t>(slot) * a.kv_heads + g) * RB;
+                // rows of the unit that hold tokens of the partition, less one
+                const int32_t last = max(min(end - 1 - (t0 + 8 * half), 7), 0);
+#pragma unroll
+                for (int i = 0; i < IPU; ++i) {
+                    const int j = half * IPU + i;
+                    const uint32_t row = min(static_cast<uint32_t>(i * RPL) + lrow, static_cast<uint32_t>(last));
+                    const uint32_t off = row * row_bytes;
+                    load_rows(j, kbase + base + off + 16 * (lslot ^ kswz(j * RPL + lrow)),
+                              vbase + base + off + 16 * lslot);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < KS; ++j) {
+                const uint32_t tl = j * RPL + lrow;
+                const int32_t t = min(t0 + static_cast<int32_t>(tl), end - 1);
+                const uint64_t row = (static_cast<uint64_t>(sh_blk[t / bs - first_blk]) * a.block_size + t % bs) *
+                                         a.kv_heads + g;
+                load_rows(j, kbase + (row * D + 8 * (lslot ^ kswz(tl))) * 2, vbase + (row * D + 8 * lslot) * 2);
+            }
         }
     };
     // A migrating launch: stores the group's rows that belong to the stage's
@@ -359,20 +483,33 @@ attn_partial_mfma(const AttnArgs a)
             reinterpret_cast<const uint8_t *>(table_entry(a.dst_tab, layer)), a.dst_layer_bytes);
         const __amdgpu_buffer_rsrc_t rv = tile_rsrc(
             reinterpret_cast<const uint8_t *>(table_entry(a.dst_tab, a.num_layers + layer)), a.dst_layer_bytes);
-        const uint32_t tile = a.block_size * a.kv_heads * RB;
-        const int32_t bs = static_cast<int32_t>(a.block_size);
-        const int32_t q = tg / bs, r0 = tg - q * bs;          // the group's first token: block, slot
         uint32_t off[KS];
         u32x4 r[KS];
+        if constexpr (UNITS) {
+            const uint32_t u0 = static_cast<uint32_t>(tg - tg0) / 32u;
 #pragma unroll
-        for (int j = 0; j < KS; ++j) {
-            const int32_t tl = j * RPL + static_cast<int32_t>(lane / LPR);
-            const int32_t s = r0 + tl, bo = s / bs, slot = s - bo * bs;
-            const int32_t d = tg + tl < end ? sh_dst[q + bo - first_blk] : -1;
-            off[j] = d < 0 ? kDropped
-                           : static_cast<uint32_t>(d) * tile + (static_cast<uint32_t>(slot) * a.kv_heads + g) * RB;
-            r[j] = *reinterpret_cast<const u32x4 *>(kbuf + j * 1024 + lane * 16);
+            for (int j = 0; j < KS; ++j) {
+                const int32_t d = static_cast<int32_t>(__builtin_amdgcn_readlane(unit_dst, u0 + j / IPU));
+                const uint32_t row = (j % IPU) * RPL + lrow;
+                off[j] = d < 0 || tg + j * RPL + static_cast<int32_t>(lrow) >= end
+                             ? kDropped
+                             : (static_cast<uint32_t>(d) * a.kv_heads + g) * RB + row * row_bytes;
+            }
+        } else {
+            const uint32_t tile = a.block_size * row_bytes;
+            const int32_t q = tg / bs, r0 = tg - q * bs;          // the group's first token: block, slot
+#pragma unroll
+            for (int j = 0; j < KS; ++j) {
+                const int32_t tl = j * RPL + static_cast<int32_t>(lrow);
+                const int32_t s = r0 + tl, bo = s / bs, slot = s - bo * bs;
+                const int32_t d = tg + tl < end ? sh_dst[q + bo - first_blk] : -1;
+                off[j] = d < 0 ? kDropped
+                               : static_cast<uint32_t>(d) * tile + (static_cast<uint32_t>(slot) * a.kv_heads + g) * RB;
+            }
         }
+#pragma unroll
+        for (int j = 0; j < KS; ++j)
+            r[j] = *reinterpret_cast<const u32x4 *>(kbuf + j * 1024 + lane * 16);
         __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
 #pragma unroll
         for (int j = 0; j < KS; ++j)
@@ -385,7 +522,6 @@ attn_partial_mfma(const AttnArgs a)
         for (int j = 0; j < KS; ++j)
             buffer_store16(rv, off[j] + 16 * (lane % LPR), r[j]);
     };
-    const int32_t tg0 = start + 16 * static_cast<int32_t>(wave);
     if (tg0 < end)
         request_group(tg0);
     for (int32_t tg = tg0; tg < end; tg += 64) {
@@ -394,8 +530,7 @@ attn_partial_mfma(const AttnArgs a)
         // a migrating launch stores the stage's rows first, while no operand
         // fragments are live yet; a group none of whose tokens lies in the
         // stage's blocks skips it (a wavefront-uniform test)
-        if (MIG && mig && (tg + 15) / static_cast<int32_t>(a.block_size) >= a.mig_from &&
-            tg / static_cast<int32_t>(a.block_size) < a.mig_to)
+        if (MIG && mig && (tg + 15) / bs >= a.mig_from && tg / bs < a.mig_to)
             store_group(tg);
         // K fragments (A operand: token r16, dims 32*ks + 8*g4 .. +8)
         u32x4 kf[KS];
@@ -454,72 +589,157 @@ attn_partial_mfma(const AttnArgs a)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             acc[mt] = acc[mt] * c;
-            acc[mt] = mfma_pv<BF16>(vf[mt], ph, acc[mt]);
-            acc[mt] = mfma_pv<BF16>(vf[mt], pl, acc[mt]);
+            acc[mt] = mfma_pv<BF16>(vf[mt], ph, pl, acc[mt]);
         }
     }
 
-    // merge the four wavefronts: state of query row r16, O^T rows 16*mt + 4*g4 + i
-    __syncthreads();                                // every wave is done with its V^T region
-    float *so = reinterpret_cast<float *>(smem);    // [wave][dim][16]
+    // Merge the four wavefronts (each holds, of query row r16, its maximum,
+    // its weight sum and O^T rows 16*mt + 4*g4 + i) through LDS, as rows of
+    // kMergeRow floats, so that the results leave in whole rows: a workgroup
+    // ends only when its stores are acknowledged, and scattered 64-byte
+    // pieces kept it waiting.
+    __syncthreads();                                // every wave is done with its rows
+    float *so = reinterpret_cast<float *>(smem);    // [wave][query row][kMergeRow]
     if (g4 == 0) {
         sh_m[wave][r16] = m;
         sh_l[wave][r16] = lsum;
     }
+    if (r16 < G) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            so[(wave * D + 16 * mt + 4 * g4 + i) * 16 + r16] = acc[mt][i];
+        for (int mt = 0; mt < MT; ++mt)
+            *reinterpret_cast<f32x4_t *>(so + (wave * 16 + r16) * kMergeRow + 16 * mt + 4 * g4) = acc[mt];
+    }
     __syncthreads();
-    if (wave == 0 && r16 < G) {
+    // the sequence's output if it is one partition, else a record; of the
+    // group's query heads
+    const bool whole = parts == 1;
+    const uint32_t out_row = whole ? D : D + kAttnHeader, out_at = whole ? 0u : kAttnHeader;
+    const uint64_t out_first = whole ? static_cast<uint64_t>(layer) * a.batch + b
+                                     : static_cast<uint64_t>(layer) * a.n_records + item;
+    const __amdgpu_buffer_rsrc_t ro = tile_rsrc(
+        reinterpret_cast<const uint8_t *>((whole ? a.out : a.ws) + (out_first * a.q_heads + g * G) * out_row),
+        G * out_row * 4);
+    auto put = [&](uint32_t at, f32x4_t v) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ro, at * 4, 0, kResultStore);
+    };
+    for (uint32_t x = threadIdx.x; x < G * (D / 4); x += kThreads) {
+        const uint32_t row = x / (D / 4), d4 = x % (D / 4);
         float mm = -INFINITY;
+#pragma unroll
         for (int w = 0; w < 4; ++w)
-            mm = fmaxf(mm, sh_m[w][r16]);
-        float cw[4], ll = 0.f;
+            mm = fmaxf(mm, sh_m[w][row]);
+        float ll = 0.f;
+        f32x4_t o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
         for (int w = 0; w < 4; ++w) {
-            cw[w] = mm == -INFINITY ? 0.f : exp2f(sh_m[w][r16] - mm);
-            ll += sh_l[w][r16] * cw[w];
+            const float c = mm == -INFINITY ? 0.f : exp2f(sh_m[w][row] - mm);
+            ll += sh_l[w][row] * c;
+            o += *reinterpret_cast<const f32x4_t *>(so + (w * 16 + row) * kMergeRow + 4 * d4) * c;
         }
-        const uint64_t slot = (static_cast<uint64_t>(layer) * a.n_items_total + a.item_base + item) * a.q_heads +
-                              g * G + r16;
-        float *dst = a.ws + slot * (D + kAttnHeader);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            float o[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t dim = 16 * mt + 4 * g4 + i;
-                o[i] = 0.f;
-                for (int w = 0; w < 4; ++w)
-                    o[i] += so[(w * D + dim) * 16 + r16] * cw[w];
-            }
-            *reinterpret_cast<float4 *>(dst + kAttnHeader + 16 * mt + 4 * g4) = make_float4(o[0], o[1], o[2], o[3]);
-        }
-        if (g4 == 0) {
-            // the reduce kernel merges with natural exponentials: store m in that base
-            dst[0] = mm == -INFINITY ? -INFINITY : mm / kLog2e;
-            dst[1] = ll;
-        }
+        if (whole && ll > 0.f)
+            o = o / ll;
+        put(row * out_row + out_at + 4 * d4, o);
+        // the reduce kernel merges with natural exponentials: m in that base
+        if (!whole && d4 == 0)
+            put(row * out_row, f32x4_t{mm == -INFINITY ? -INFINITY : mm / kLog2e, ll, 0.f, 0.f});
     }
 }
 
 template <int BF16, int D>
-const void *attn_kernel(int group, bool migrating)
+const void *attn_kernel(bool migrating, bool units)
+{
+    if (migrating)
+        return units ? reinterpret_cast<const void *>(&attn_partial_mfma<BF16, D, 1, 1>)
+                     : reinterpret_cast<const void *>(&attn_partial_mfma<BF16, D, 1, 0>);
+    return units ? reinterpret_cast<const void *>(&attn_partial_mfma<BF16, D, 0, 1>)
+                 : reinterpret_cast<const void *>(&attn_partial_mfma<BF16, D, 0, 0>);
+}
+
+const void *attn_kernel_for(int bf16, int head_dim, int group, bool migrating, bool units)
 {
     if (group < 1 || group > 16 || (group & (group - 1)) != 0)
         return nullptr;
-    return migrating ? reinterpret_cast<const void *>(&attn_partial_mfma<BF16, D, 1>)
-                     : reinterpret_cast<const void *>(&attn_partial_mfma<BF16, D, 0>);
+    if (head_dim == 64)
+        return bf16 ? attn_kernel<1, 64>(migrating, units) : attn_kernel<0, 64>(migrating, units);
+    if (head_dim == 128)
+        return bf16 ? attn_kernel<1, 128>(migrating, units) : attn_kernel<0, 128>(migrating, units);
+    return nullptr;
 }
 
-const void *attn_kernel_for(int bf16, int head_dim, int group, bool migrating)
+// ---------------------------------------------------------------------------
+// How a call is cut into partitions.
+
+// Partitions of a sequence of n tokens, at most `part` tokens each.
+inline uint32_t attn_parts(int32_t n, int32_t part)
 {
-    if (head_dim == 64)
-        return bf16 ? attn_kernel<1, 64>(group, migrating) : attn_kernel<0, 64>(group, migrating);
-    if (head_dim == 128)
-        return bf16 ? attn_kernel<1, 128>(group, migrating) : attn_kernel<0, 128>(group, migrating);
-    return nullptr;
+    if (n <= part)
+        return 1u;
+    const uint32_t parts = static_cast<uint32_t>((static_cast<int64_t>(n) + part - 1) / part);
+    const int32_t len = attn_part_len(n, parts);     // rounded up to 64: perhaps fewer are enough
+    return static_cast<uint32_t>((static_cast<int64_t>(n) + len - 1) / len);
+}
+
+// Bytes of the partial results of a call (sequences of one partition leave none).
+inline int attn_record_bytes(const int32_t *ctx_lens, int32_t batch, int32_t part, int64_t num_layers,
+                             int64_t q_heads, int64_t head_dim, int64_t *bytes)
+{
+    int64_t n = 0, v = 0;
+    for (int32_t b = 0; b < batch; ++b) {
+        const uint32_t parts = attn_parts(ctx_lens[b], part);
+        n += parts > 1 ? parts : 0;
+    }
+    if (__builtin_mul_overflow(num_layers, n, &v) || __builtin_mul_overflow(v, q_heads, &v) ||
+        __builtin_mul_overflow(v, (head_dim + kAttnHeader) * 4, &v))
+        return LLMIG_EINVAL;
+    *bytes = v;
+    return LLMIG_OK;
+}
+
+// Most tokens per partition of a call: kPartTokens, unless that leaves the
+// chip short of workgroups.  A partition costs a workgroup's start and end
+// (block ids, query rows, the first rows' latency, the merge, a record) and a
+// share of the merge kernel, so longer is better as long as every CU has
+// work: shares of about kAttnWorkgroups workgroups, two a CU.  Measured, one
+// layer of 8 KV heads: one sequence of 32000 tokens, partitions of 2048 / 1024
+// / 512 / 256 tokens 42 / 28.6 / 30.1 / 31.9 us; three of up to 3000, 2048 /
+// 512 / 128 31.4 / 15.8 / 14.1 us; 32 layers of one sequence of 32000, 2048 /
+// 1024 / 512 703 / 729 / 773 us.  Records of a finer split stay within
+// kSplitBytes, half of LLMIG_DECODE_SCRATCH_BYTES, so that every entry point
+// cuts a call alike.
+constexpr int64_t kAttnWorkgroups = 512;
+constexpr int64_t kSplitBytes = LLMIG_DECODE_SCRATCH_BYTES / 2;
+
+inline int32_t attn_part_tokens(const int32_t *ctx_lens, int32_t batch, int64_t num_layers, int64_t kv_heads,
+                                int64_t q_heads, int64_t head_dim)
+{
+    int64_t tokens = 0, work = 0;
+    for (int32_t b = 0; b < batch; ++b)
+        tokens += ctx_lens[b];
+    if (__builtin_mul_overflow(tokens, num_layers, &work) || __builtin_mul_overflow(work, kv_heads, &work) ||
+        work >= kAttnWorkgroups * kPartTokens)
+        return kPartTokens;
+    int32_t part = static_cast<int32_t>((work / kAttnWorkgroups + 63) / 64 * 64);
+    part = std::max(std::min(part, kPartTokens), kMinPartTokens);
+    int64_t bytes = 0;
+    while (part < kPartTokens &&
+           (attn_record_bytes(ctx_lens, batch, part, num_layers, q_heads, head_dim, &bytes) != LLMIG_OK ||
+            bytes > kSplitBytes))
+        part = std::min(2 * part, kPartTokens);
+    return part;
+}
+
+// The merge kernel for at most `most` partitions a sequence; returns its rows
+// per workgroup.
+inline uint32_t attn_reduce_kernel(int head_dim, uint32_t most, const void **fn)
+{
+    if (head_dim == 64) {
+        *fn = most <= 8 ? reinterpret_cast<const void *>(&attn_reduce<64, 1>)
+                        : reinterpret_cast<const void *>(&attn_reduce<64, 16>);
+        return most <= 8 ? kThreads / 16 : 1;
+    }
+    *fn = most <= 8 ? reinterpret_cast<const void *>(&attn_reduce<128, 1>)
+                    : reinterpret_cast<const void *>(&attn_reduce<128, 8>);
+    return most <= 8 ? kThreads / 32 : 1;
 }
 
 } // namespace

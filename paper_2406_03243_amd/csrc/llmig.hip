@@ -1016,7 +1016,7 @@ static int attn_check(const llmig_pool *pool, int32_t dtype, const void *q, int3
     const int32_t hkv = pool->num_kv_heads;
     if (q_heads % hkv != 0)
         return LLMIG_EINVAL;
-    *fn = attn_kernel_for(dtype, pool->head_dim, q_heads / hkv, migrating);
+    *fn = attn_kernel_for(dtype, pool->head_dim, q_heads / hkv, migrating, pool->block_size % 8 == 0);
     if (!*fn || (reinterpret_cast<uintptr_t>(q) & 15u) || (reinterpret_cast<uintptr_t>(out) & 15u) ||
         (reinterpret_cast<uintptr_t>(tables) & 3u))
         return LLMIG_EINVAL;
@@ -1038,11 +1038,12 @@ struct AttnMigration {
 };
 
 // Enqueues a checked decode-attention call: the partial kernel over the
-// items, kAttnItems per launch (their ranges ride in the kernel arguments),
-// then the merge.  ws holds the partial results.  Allocates nothing.
+// items, then the merge of the sequences cut into several partitions.  ws
+// (ws_bytes, at least what partitions of kPartTokens need) holds the partial
+// results.  Allocates nothing.
 static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, int32_t batch, int32_t q_heads,
                         const int32_t *tables, int32_t table_stride, const int32_t *ctx_lens, float scale,
-                        float *ws, int64_t n_items, float *out, hipStream_t st,
+                        float *ws, int64_t ws_bytes, float *out, hipStream_t st,
                         const AttnMigration &mig = AttnMigration())
 {
     AttnArgs a;
@@ -1057,11 +1058,16 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
         a.dst_layer_bytes = static_cast<uint32_t>(static_cast<uint64_t>(mig.dst->num_blocks) * mig.dst->tile_bytes);
         a.dst_blocks = mig.dst->num_blocks;
     }
-    const size_t lds_ids = attn_blk_slots(pool->block_size) * sizeof(int32_t) * (mig.dst ? 2 : 1);
+    int32_t part = attn_part_tokens(ctx_lens, batch, pool->num_layers, pool->num_kv_heads, q_heads, pool->head_dim);
+    int64_t need = 0;
+    if (attn_record_bytes(ctx_lens, batch, part, pool->num_layers, q_heads, pool->head_dim, &need) != LLMIG_OK ||
+        need > ws_bytes)
+        part = kPartTokens;
     a.k_tab = pool->d_tab;
     a.q = static_cast<const uint8_t *>(q);
     a.tables = tables;
     a.ws = ws;
+    a.out = out;
     a.scale = scale;
     a.num_layers = static_cast<uint32_t>(pool->num_layers);
     a.batch = static_cast<uint32_t>(batch);
@@ -1069,53 +1075,67 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
     a.kv_heads = static_cast<uint32_t>(pool->num_kv_heads);
     a.block_size = static_cast<uint32_t>(pool->block_size);
     a.table_stride = static_cast<uint32_t>(table_stride);
-    a.n_items_total = static_cast<uint32_t>(n_items);
-    uint32_t m = 0, first = 0;
-    auto flush = [&]() -> hipError_t {
-        if (m == 0)
-            return hipSuccess;
-        a.item_base = first;
-        a.items = m;
-        void *args[] = {&a};
-        hipError_t e = hipLaunchKernel(fn, dim3(m * a.kv_heads, a.num_layers), dim3(kThreads), args, lds_ids, st);
-        first += m;
-        m = 0;
-        return e;
-    };
-    for (int32_t b = 0; b < batch; ++b)
-        for (int32_t t = 0; t < ctx_lens[b]; t += kPartTokens) {
-            a.item_seq[m] = b;
-            a.item_start[m] = t;
-            a.item_end[m] = std::min(ctx_lens[b], t + kPartTokens);
-            if (++m == static_cast<uint32_t>(kAttnItems)) {
-                hipError_t e = flush();
-                if (e != hipSuccess)
-                    return hip_error(e);
-            }
-        }
-    hipError_t e = flush();
-    if (e != hipSuccess)
-        return hip_error(e);
+    a.part_tokens = static_cast<uint32_t>(part);
+    // launch order: several partitions first, longest partition first
+    uint64_t key[kAttnMaxBatch];
+    for (int32_t b = 0; b < batch; ++b) {
+        const uint32_t parts = attn_parts(ctx_lens[b], part);
+        const uint64_t len = static_cast<uint64_t>(parts > 1 ? attn_part_len(ctx_lens[b], parts) : ctx_lens[b]);
+        key[b] = (parts > 1 ? 0ull : 1ull << 63) | (0x7fffffffull - len) << 32 | static_cast<uint64_t>(b);
+    }
+    std::sort(key, key + batch);
     AttnReduceArgs r;
     std::memset(&r, 0, sizeof(r));
+    uint32_t items = 0, most = 0;
+    for (int32_t s = 0; s < batch; ++s) {
+        const int32_t b = static_cast<int32_t>(key[s] & 0xffffffffull);
+        const uint32_t parts = attn_parts(ctx_lens[b], part);
+        items += parts;
+        a.item_end[s] = items;
+        a.ctx[s] = ctx_lens[b];
+        a.seq[s] = static_cast<uint8_t>(b);
+        if (parts > 1) {
+            most = std::max(most, parts);
+            r.seq_end[s] = items;
+            r.seq[s] = static_cast<uint8_t>(b);
+            r.seqs = static_cast<uint32_t>(s) + 1u;
+            a.n_records = items;
+        }
+    }
+    const size_t lds_ids = pool->block_size % 8 == 0
+                               ? 0
+                               : attn_blk_slots(a.part_tokens, a.block_size) * sizeof(int32_t) * (mig.dst ? 2 : 1);
+    const uint64_t per_item = static_cast<uint64_t>(a.kv_heads) * a.num_layers;
+    const uint32_t step = static_cast<uint32_t>(std::max<uint64_t>(kMaxGridWorkgroups / per_item, 1u));
+    for (uint32_t at = 0; at < items; at += std::min(step, items - at)) {
+        a.item_base = at;
+        void *args[] = {&a};
+        hipError_t e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(std::min(step, items - at) * per_item)),
+                                       dim3(kThreads), args, lds_ids, st);
+        if (e != hipSuccess)
+            return hip_error(e);
+    }
+    if (r.seqs == 0)
+        return LLMIG_OK;
     r.ws = ws;
     r.out = out;
     r.num_layers = a.num_layers;
     r.batch = a.batch;
     r.q_heads = a.q_heads;
     r.head_dim = static_cast<uint32_t>(pool->head_dim);
-    r.n_items_total = a.n_items_total;
-    for (int32_t b = 0, i = 0; b < batch; ++b) {
-        r.seq_first[b] = i;
-        r.seq_count[b] = (ctx_lens[b] + kPartTokens - 1) / kPartTokens;
-        i += r.seq_count[b];
+    r.n_records = a.n_records;
+    const uint64_t rows = static_cast<uint64_t>(r.num_layers) * r.seqs * r.q_heads;
+    const void *rfn = nullptr;
+    const uint64_t per_wg = attn_reduce_kernel(pool->head_dim, most, &rfn);
+    for (r.row_base = 0; r.row_base < rows; r.row_base += kMaxGridWorkgroups * per_wg) {
+        const uint64_t grid = (rows - r.row_base + per_wg - 1) / per_wg;
+        void *rargs[] = {&r};
+        const hipError_t e = hipLaunchKernel(rfn, dim3(static_cast<uint32_t>(std::min<uint64_t>(grid, kMaxGridWorkgroups))),
+                                             dim3(kThreads), rargs, 0, st);
+        if (e != hipSuccess)
+            return hip_error(e);
     }
-    // one lane per four dimensions of an output row
-    const uint64_t total = static_cast<uint64_t>(pool->num_layers) * batch * q_heads * (pool->head_dim / 4);
-    const uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>((total + kThreads - 1) / kThreads, 1u << 20));
-    void *rargs[] = {&r};
-    e = hipLaunchKernel(reinterpret_cast<const void *>(&attn_reduce), dim3(grid), dim3(kThreads), rargs, 0, st);
-    return e == hipSuccess ? LLMIG_OK : hip_error(e);
+    return LLMIG_OK;
 }
 
 int llmig_decode_attention_workspace(const int32_t *ctx_lens, int32_t batch, int32_t num_layers, int32_t q_heads,
@@ -1129,7 +1149,18 @@ int llmig_decode_attention_workspace(const int32_t *ctx_lens, int32_t batch, int
     int64_t n_items = 0;
     if (attn_item_count(ctx_lens, batch, &n_items) != LLMIG_OK)
         return LLMIG_EINVAL;
-    return attn_workspace_bytes(num_layers, n_items, q_heads, head_dim, bytes);
+    int64_t need = 0;
+    int rc = attn_workspace_bytes(num_layers, n_items, q_heads, head_dim, &need);
+    // what the split for any number of KV heads takes
+    for (int32_t group = 1; rc == LLMIG_OK && group <= 16 && q_heads % group == 0; group *= 2) {
+        int64_t v = 0;
+        const int32_t part = attn_part_tokens(ctx_lens, batch, num_layers, q_heads / group, q_heads, head_dim);
+        rc = attn_record_bytes(ctx_lens, batch, part, num_layers, q_heads, head_dim, &v);
+        need = std::max(need, v);
+    }
+    if (rc == LLMIG_OK)
+        *bytes = need;
+    return rc;
 }
 
 int llmig_decode_attention(const llmig_pool *pool, int32_t dtype, const void *q, int32_t batch, int32_t q_heads,
@@ -1144,7 +1175,7 @@ int llmig_decode_attention(const llmig_pool *pool, int32_t dtype, const void *q,
     if ((reinterpret_cast<uintptr_t>(workspace) & 15u) || (n_items > 0 && (!workspace || workspace_bytes < need)))
         return LLMIG_EINVAL;
     return attn_enqueue(pool, fn, q, batch, q_heads, tables, table_stride, ctx_lens, scale,
-                        static_cast<float *>(workspace), n_items, out, static_cast<hipStream_t>(stream));
+                        static_cast<float *>(workspace), workspace_bytes, out, static_cast<hipStream_t>(stream));
 }
 
 int llmig_decode_attention_migrate(const llmig_pool *pool, int32_t dtype, const void *q, int32_t batch,
@@ -1181,7 +1212,7 @@ int llmig_decode_attention_migrate(const llmig_pool *pool, int32_t dtype, const 
     mig.from = static_cast<int32_t>(from_block);
     mig.to = static_cast<int32_t>(to_block);
     return attn_enqueue(pool, fn, q, batch, q_heads, tables, table_stride, ctx_lens, scale,
-                        static_cast<float *>(workspace), n_items, out, static_cast<hipStream_t>(stream), mig);
+                        static_cast<float *>(workspace), workspace_bytes, out, static_cast<hipStream_t>(stream), mig);
 }
 
 int llmig_decode_attention_noalloc(const llmig_pool *pool, int32_t dtype, const void *q, int32_t batch,
@@ -1202,7 +1233,7 @@ int llmig_decode_attention_noalloc(const llmig_pool *pool, int32_t dtype, const 
         if (rc != LLMIG_OK)
             return rc;
         return attn_enqueue(pool, fn, q, batch, q_heads, tables, table_stride, ctx_lens, scale,
-                            static_cast<float *>(ws), n_items, out, static_cast<hipStream_t>(stream));
+                            static_cast<float *>(ws), LLMIG_DECODE_SCRATCH_BYTES, out, static_cast<hipStream_t>(stream));
     });
 }
 
