@@ -93,6 +93,8 @@ struct ConvertArgs {
     uint32_t first_unit;        // this launch's first slab (convert_slabs)
     uint32_t lin_first;         // this launch's first pair within the whole call
     uint32_t lin_pairs;         // pairs in the whole call (plane stride of the staging buffer)
+    uint32_t first_slot;        // write_slabs: slot of the launch's first token in its block
+    uint32_t tokens;            // write_slabs: tokens in this launch
     int32_t layouts[4];         // source K, source V, destination K, destination V
     uint32_t ids[2 * kInlinePairs]; // inline ids, laid out as the launch's Ids mode says
 };
@@ -185,6 +187,16 @@ __device__ __forceinline__ u32x4 gather_chunk(const u32x4 *slab, uint32_t k, int
     return slab[padded(dim_chunk_index(sl, t, c, a))];
 }
 
+// Slab of workgroup w (kSlabRun consecutive slabs on one XCD; the dispatcher
+// hands workgroup g to XCD g % 8; the grid's tail keeps its order).
+__device__ __forceinline__ uint32_t slab_of(uint32_t w)
+{
+    const uint32_t round = w / (kXcds * kSlabRun), r8 = w % (kXcds * kSlabRun);
+    if ((round + 1u) * (kXcds * kSlabRun) <= gridDim.x)
+        w = round * (kXcds * kSlabRun) + (r8 % kXcds) * kSlabRun + r8 / kXcds;
+    return w;
+}
+
 // One workgroup per slab, one 16-byte chunk per lane (WAVES wavefronts cover
 // the slab; the launch leaves out those past its end).
 template <int IDS, int WAVES>
@@ -192,13 +204,7 @@ __global__ void __launch_bounds__(WAVES * 64) convert_slabs(const ConvertArgs a)
 {
     __shared__ u32x4 lds[68 * WAVES];                // 64 WAVES chunks + one pad per 16
     const uint32_t k = threadIdx.x;
-    uint32_t w = blockIdx.x;
-    // the dispatcher hands workgroup g to XCD g % 8: renumbered so that each
-    // XCD takes kSlabRun consecutive slabs (the grid's tail keeps its order)
-    const uint32_t round = w / (kXcds * kSlabRun), r8 = w % (kXcds * kSlabRun);
-    if ((round + 1u) * (kXcds * kSlabRun) <= gridDim.x)
-        w = round * (kXcds * kSlabRun) + (r8 % kXcds) * kSlabRun + r8 / kXcds;
-    const uint32_t unit = a.first_unit + w;
+    const uint32_t unit = a.first_unit + slab_of(blockIdx.x);
     const uint32_t tile = unit / a.heads;
     const uint32_t h = unit - tile * a.heads;
     const uint32_t plane = tile / a.pairs;
@@ -232,6 +238,66 @@ __global__ void __launch_bounds__(WAVES * 64) convert_slabs(const ConvertArgs a)
     __syncthreads();
     if (in)
         buffer_store16(rd, to, gather_chunk(lds, k, sl, dl, a));
+}
+
+// Token writes: the slab of one head of the launch's block i receives the
+// tokens that data (a.src_lin, [L][K,V][a.lin_pairs tokens][heads][head_dim])
+// holds of that block: slots [lo, hi).  As convert_slabs from a token-major
+// source, with what lies outside those slots left alone: a chunk is one
+// token's in NHD, HND and HCNX; in HDN it is 8 tokens' and is stored element
+// by element where not all 8 are written.
+template <int WAVES>
+__global__ void __launch_bounds__(WAVES * 64) write_slabs(const ConvertArgs a)
+{
+    __shared__ u32x4 lds[68 * WAVES];
+    const uint32_t k = threadIdx.x;
+    const uint32_t unit = a.first_unit + slab_of(blockIdx.x);
+    const uint32_t tile = unit / a.heads;
+    const uint32_t h = unit - tile * a.heads;
+    const uint32_t plane = tile / a.pairs;
+    const uint32_t i = tile - plane * a.pairs;
+    const uint32_t layer = plane >> 1, kv = plane & 1u;
+    const int32_t dl = a.layouts[2 + kv];
+    const uint32_t lo = i == 0 ? a.first_slot : 0u;
+    const uint32_t hi = min(a.block_size, a.first_slot + a.tokens - i * a.block_size);
+    // the row that slot 0 of the block would have in data (slots before lo are not read)
+    const uint8_t *s = a.src_lin + ((static_cast<uint64_t>(plane) * a.lin_pairs + a.lin_first) * a.heads + h) *
+                                       (a.row_chunks * 16u) +
+                       (static_cast<int64_t>(i) * a.block_size - a.first_slot) *
+                           static_cast<int64_t>(a.heads * a.row_chunks * 16u);
+    uint8_t *d = reinterpret_cast<uint8_t *>(table_entry(a.dst_tab, kv * a.num_layers + layer)) +
+                 static_cast<uint64_t>(uniform(a.ids[i])) * a.tile_bytes;
+    const __amdgpu_buffer_rsrc_t rd = tile_rsrc(d, a.tile_bytes);
+    const uint32_t t = div_magic(k, a.magic_row);
+    const bool in = k < a.chunks && t >= lo && t < hi;
+    u32x4 r = {0u, 0u, 0u, 0u};
+    if (in)
+        r = load16(s + slab_offset(LLMIG_LAYOUT_NHD, 0, k, a));
+    if (dl <= LLMIG_LAYOUT_HND) {
+        buffer_store16(rd, in ? slab_offset(dl, h, k, a) : kOutOfRange, r);
+        return;
+    }
+    lds[padded(k)] = r;
+    __syncthreads();
+    if (k >= a.chunks)
+        return;
+    const uint32_t to = slab_offset(dl, h, k, a);
+    const u32x4 v = gather_chunk(lds, k, LLMIG_LAYOUT_NHD, dl, a);
+    if (dl == LLMIG_LAYOUT_HCNX) {
+        const uint32_t slot = k - div_magic(k, a.magic_bs) * a.block_size;
+        buffer_store16(rd, slot >= lo && slot < hi ? to : kOutOfRange, v);
+        return;
+    }
+    const uint32_t t0 = 8u * (k - div_magic(k, a.magic_t) * a.t_chunks);
+    if (t0 >= lo && t0 + 8u <= hi) {
+        buffer_store16(rd, to, v);
+        return;
+    }
+    const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e)
+        if (t0 + e >= lo && t0 + e < hi)
+            *(LLMIG_GLOBAL uint16_t *)(d + to + 2u * e) = static_cast<uint16_t>(w4[e / 2] >> (16u * (e & 1u)));
 }
 
 // A capped grid: kConvertWaves wavefronts walk the slabs, N chunks per lane.
@@ -338,6 +404,22 @@ const void *convert_kernel_waves(int waves)
     }
 }
 
+const void *write_kernel(int waves)
+{
+    switch (waves) {
+    case 16:
+        return reinterpret_cast<const void *>(&write_slabs<16>);
+    case 8:
+        return reinterpret_cast<const void *>(&write_slabs<8>);
+    case 4:
+        return reinterpret_cast<const void *>(&write_slabs<4>);
+    case 2:
+        return reinterpret_cast<const void *>(&write_slabs<2>);
+    default:
+        return reinterpret_cast<const void *>(&write_slabs<1>);
+    }
+}
+
 const void *convert_kernel(int ids, int n, bool capped)
 {
     if (capped)
@@ -350,6 +432,13 @@ const void *convert_kernel(int ids, int n, bool capped)
 uint64_t magic_for(uint32_t divisor)
 {
     return ((1ull << 32) + divisor - 1) / divisor;
+}
+
+void convert_magic(ConvertArgs &a)
+{
+    a.magic_row = magic_for(a.row_chunks);
+    a.magic_bs = magic_for(a.block_size);
+    a.magic_t = magic_for(a.t_chunks > 0 ? a.t_chunks : 1u);
 }
 
 // Chunks per lane (a power of two) for slabs of `chunks` 16-byte chunks.
@@ -377,9 +466,7 @@ int launch_convert(ConvertArgs a, const int32_t *src_ids, const int32_t *dst_ids
     const int per_lane = convert_chunks_per_lane(a.chunks);
     if (per_lane > kMaxSlabChunksPerLane)
         return LLMIG_EINVAL;
-    a.magic_row = magic_for(a.row_chunks);
-    a.magic_bs = magic_for(a.block_size);
-    a.magic_t = magic_for(a.t_chunks > 0 ? a.t_chunks : 1u);
+    convert_magic(a);
     const uint64_t units_per_pair = 2ull * a.num_layers * a.heads;
     const uint64_t per_launch = std::min<uint64_t>(0x7fffffffull / units_per_pair,
                                                    ids_on_device ? UINT64_MAX : inline_pairs);

@@ -61,7 +61,21 @@ __device__ __align__(256) uint8_t scratch[LLMIG_DECODE_SCRATCH_BYTES];
 
 namespace {
 
-// Decode stand-in: writes whole token slots through a block table.
+// Token writes (llmig_write_tokens).  Three kernels:
+//  * write_rows, token-major pools, prompts and slots under 2 KiB: the tokens
+//    of a block are one run of bytes in data and in the tile; a wavefront
+//    moves 1 KiB of it, tensor by tensor (see copy_tiles.h for why so little).
+//  * write_slabs (convert_tiles.h), other layouts from kSlabWriteTokens tokens
+//    on: a head's slab of a block goes through LDS, so the stores are whole
+//    chunks in the tile's own order.
+//  * write_token_slots, the rest (a few tokens; slabs over 16 KiB; HDN with
+//    a block size that 8 does not divide): a token and tensor per workgroup,
+//    16-byte loads, stores where the layout puts each piece (HDN: 2 bytes at
+//    a time).
+// Measured on MI355X against write_token_slots alone, 2000 tokens, 32 layers
+// of 32 heads of 128: token-major 380 -> 315 us (6.7 TB/s read + written),
+// head-major 393 -> 319, HCNX keys and HDN values 2221 -> 325; one head 78 ->
+// 11.7, 79 -> 12.2, 97 -> 12.8.
 struct WriteArgs {
     const uint64_t *tab;
     const uint8_t *data;
@@ -76,6 +90,9 @@ struct WriteArgs {
     uint32_t first_token;  // this launch's first token within the call
     uint32_t tokens;       // tokens in this launch
     uint32_t first_slot;   // slot of this launch's first token within its block
+    uint32_t blocks;       // blocks this launch touches
+    uint32_t rows_per_run; // write_rows: KiB of the longest run of a block's tokens
+    uint32_t first_item;   // write_rows: this launch's first KiB
     int32_t ids[kInlinePairs]; // blocks this launch touches, in logical order
 };
 
@@ -122,6 +139,28 @@ __global__ void __launch_bounds__(kThreads) write_token_slots(const WriteArgs a)
     }
 }
 
+// One wavefront per KiB of a block's run of tokens, all layers and K/V.
+__global__ void __launch_bounds__(64) write_rows(const WriteArgs a)
+{
+    const uint32_t item = a.first_item + blockIdx.x;
+    const uint32_t run = item / a.rows_per_run;
+    const uint32_t row = item - run * a.rows_per_run;
+    const uint32_t plane = run / a.blocks;
+    const uint32_t i = run - plane * a.blocks;
+    const uint32_t layer = plane >> 1, kv = plane & 1u;
+    const uint32_t lo = i == 0 ? a.first_slot : 0u;
+    const uint32_t hi = min(a.block_size, a.first_slot + a.tokens - i * a.block_size);
+    const uint32_t bytes = (hi - lo) * a.slot_bytes;
+    const uint32_t off = row * 1024u + threadIdx.x * 16u;
+    const uint8_t *s = a.data + (static_cast<uint64_t>(plane) * a.data_tokens + a.first_token +
+                                 (i * a.block_size + lo - a.first_slot)) * a.slot_bytes;
+    uint8_t *d = reinterpret_cast<uint8_t *>(table_entry(a.tab, kv * a.num_layers + layer)) +
+                 static_cast<uint64_t>(uniform(static_cast<uint32_t>(a.ids[i]))) * a.tile_bytes +
+                 static_cast<uint64_t>(lo) * a.slot_bytes;
+    // lanes past the run: out of the resources' range
+    buffer_store16(tile_rsrc(d, bytes), off, buffer_load16(tile_rsrc(s, bytes), off));
+}
+
 // Harness: a steady stream of HBM reads standing in for decode's KV reads.
 // Each lane sums (as 32-bit integers) the 16-byte words it reads and stores
 // its own result to out[global lane]; every lane runs a fixed number of
@@ -160,6 +199,18 @@ __global__ void __launch_bounds__(64) signal_host(uint64_t *slot, uint64_t ticke
     if (threadIdx.x == 0)
         __hip_atomic_store(slot, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+
+// Token-major writes up to this size (what decoding appends), of slots that
+// fill a workgroup, keep a token and tensor per workgroup: beside a migration's
+// first stage their few workgroups and cached stores cost the stage less (a
+// migration of 8192 + 4 x 37 tokens of a 7B shape 1363-1368 us against
+// 1376-1381 with rows).
+constexpr int64_t kSmallWriteBytes = 32 << 20;
+
+// From this many tokens on a write to a pool that is not token-major goes
+// slab by slab (32 layers of 32 heads, HCNX/HDN: 2 tokens 9.2 -> 8.8 us, 4
+// 13.1 -> 8.8, 16 33 -> 11.4; one token takes the same either way).
+constexpr int64_t kSlabWriteTokens = 2;
 
 // Runs an entry point's body.  The host code's only exceptions are failed
 // allocations (the id bitmaps, plan scratch, pool bookkeeping); they become
@@ -937,6 +988,20 @@ int llmig_write_tokens(const llmig_pool *pool, const int32_t *table, int64_t tab
     a.layouts[0] = pool->layouts[0];
     a.layouts[1] = pool->layouts[1];
     a.data_tokens = static_cast<uint32_t>(n_tok);
+    const int64_t planes = 2ll * pool->num_layers;
+    const bool rows = nhd && (slot_bytes < kRowBytes / 2 || n_tok * slot_bytes > kSmallWriteBytes / planes) &&
+                      bs * slot_bytes / 1024 < 0x3fffffffll / planes / kInlinePairs;
+    const bool slabs = !nhd && n_tok >= kSlabWriteTokens && conversion_supported(pool, pool->layouts) &&
+                       planes * pool->num_kv_heads * kInlinePairs < 0x7fffffffll;
+    ConvertArgs c;
+    if (slabs) {
+        const int32_t from[2] = {LLMIG_LAYOUT_NHD, LLMIG_LAYOUT_NHD};
+        c = convert_args(pool, from, pool->layouts);
+        convert_magic(c);
+        c.src_lin = static_cast<const uint8_t *>(data);
+        c.dst_tab = pool->d_tab;
+        c.lin_pairs = static_cast<uint32_t>(n_tok);
+    }
     // Each launch covers whole blocks' worth of tokens, at most kInlinePairs blocks.
     int64_t t = from_tok;
     while (t < from_tok + n_tok) {
@@ -946,12 +1011,43 @@ int llmig_write_tokens(const llmig_pool *pool, const int32_t *table, int64_t tab
         a.tokens = static_cast<uint32_t>(end - t);
         a.first_slot = static_cast<uint32_t>(t - blk0 * bs);
         const int64_t nblk = (end - 1) / bs - blk0 + 1;
-        std::memcpy(a.ids, table + blk0, static_cast<size_t>(nblk) * sizeof(int32_t));
-        void *args[] = {&a};
-        const uint32_t items = a.tokens * 2u * a.num_layers;
-        hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&write_token_slots),
-                                       dim3(std::min(items, kMaxGridWorkgroups)), dim3(kThreads), args, 0,
-                                       static_cast<hipStream_t>(stream));
+        hipError_t e = hipSuccess;
+        if (slabs) {
+            c.first_slot = a.first_slot;
+            c.tokens = a.tokens;
+            c.lin_first = a.first_token;
+            c.pairs = static_cast<uint32_t>(nblk);
+            std::memcpy(c.ids, table + blk0, static_cast<size_t>(nblk) * sizeof(int32_t));
+            const uint32_t threads = (c.chunks + 63u) / 64u * 64u;
+            const uint64_t units = static_cast<uint64_t>(nblk) * 2 * c.num_layers * c.heads;
+            const uint64_t step = (1u << 30) / threads;
+            void *args[] = {&c};
+            for (uint64_t at = 0; at < units && e == hipSuccess; at += step) {
+                c.first_unit = static_cast<uint32_t>(at);
+                e = hipLaunchKernel(write_kernel(convert_chunks_per_lane(c.chunks)),
+                                    dim3(static_cast<uint32_t>(std::min(step, units - at))), dim3(threads), args, 0,
+                                    static_cast<hipStream_t>(stream));
+            }
+        } else {
+            a.blocks = static_cast<uint32_t>(nblk);
+            std::memcpy(a.ids, table + blk0, static_cast<size_t>(nblk) * sizeof(int32_t));
+            void *args[] = {&a};
+            if (rows) {
+                a.rows_per_run = static_cast<uint32_t>((std::min<int64_t>(bs, a.tokens) * slot_bytes + 1023) / 1024);
+                const uint64_t items = static_cast<uint64_t>(nblk) * 2 * a.num_layers * a.rows_per_run;
+                for (uint64_t at = 0; at < items && e == hipSuccess; at += kMaxRowsPerLaunch) {
+                    a.first_item = static_cast<uint32_t>(at);
+                    e = hipLaunchKernel(reinterpret_cast<const void *>(&write_rows),
+                                        dim3(static_cast<uint32_t>(std::min<uint64_t>(kMaxRowsPerLaunch, items - at))),
+                                        dim3(64), args, 0, static_cast<hipStream_t>(stream));
+                }
+            } else {
+                const uint32_t items = a.tokens * 2u * a.num_layers;
+                e = hipLaunchKernel(reinterpret_cast<const void *>(&write_token_slots),
+                                    dim3(std::min(items, kMaxGridWorkgroups)), dim3(kThreads), args, 0,
+                                    static_cast<hipStream_t>(stream));
+            }
+        }
         if (e != hipSuccess)
             return hip_error(e);
         t = end;

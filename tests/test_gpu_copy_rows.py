@@ -116,3 +116,34 @@ def test_convert_slabs(case, dev):
         torch.cuda.synchronize()
         orc.unpack_layout(hd, dl, into, packed, sl, heads, dim, 2)
         assert image(dst).equals(hd), f"converting unpack {sl} -> {dl} differs"
+
+
+# layers, blocks, block_size, heads, head_dim, first token, tokens
+WRITE_CASES = [
+    (2, 12, 16, 3, 64, 5, 1),        # one token: no slab
+    (2, 12, 16, 3, 64, 15, 2),       # the last slot of a block and the first of the next
+    (1, 12, 16, 13, 128, 0, 32),     # whole blocks
+    (2, 12, 16, 5, 40, 3, 70),       # partial first and last blocks, 80-chunk slabs
+    (1, 300, 8, 2, 64, 4, 2100),     # 8-token units, more blocks than one launch carries
+    (1, 20, 32, 3, 128, 9, 200),     # partial 8-token units on both ends
+    (1, 20, 12, 3, 64, 7, 100),      # HDN with a block size that 8 does not divide
+    (1, 6, 128, 2, 128, 100, 400),   # slabs over 16 KiB
+    (1, 140, 16, 32, 128, 5, 2060),  # over 32 MiB of 8 KiB slots
+]
+
+
+@pytest.mark.parametrize("layouts", [(0, 0), (1, 1), (2, 3), (3, 2), (0, 3)], ids=lambda l: f"{l[0]}{l[1]}")
+@pytest.mark.parametrize("case", WRITE_CASES, ids=lambda c: f"bs{c[2]}_at{c[5]}_n{c[6]}")
+def test_write_tokens(case, layouts):
+    print("[case]", case, layouts, flush=True)
+    layers, blocks, bs, heads, dim, first, n = case
+    base = pool(wl.PoolShape(layers, blocks, bs, heads, dim, "bf16"), 90 + n, wl.DST_VALUES)
+    dst = Pool(base.k, base.v, layouts)
+    table = wl.stream(90 + n, wl.EXTRA).permutation(blocks).astype(np.int32)
+    data = wl.random_bytes(90 + n, wl.APPEND_VALUES, layers * 2 * n * heads * dim * 2).reshape(
+        layers, 2, n, heads * dim * 2)
+    hd = image(dst)
+    llmig.llmig_write_tokens(dst, table, first, torch.from_numpy(data).cuda())
+    torch.cuda.synchronize()
+    oracle.default().write_tokens_layout(hd, layouts, table, first, data, heads, dim, 2)
+    assert image(dst).equals(hd), "differs from the oracle"
