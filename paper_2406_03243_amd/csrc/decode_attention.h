@@ -57,7 +57,7 @@ struct AttnArgs {
     uint32_t part_tokens;       // most tokens of a partition in this call
     uint32_t item_end[kAttnMaxBatch];  // items of the first s + 1 sequences
     int32_t ctx[kAttnMaxBatch];        // tokens of sequence s
-    uint8_t seq[kAttnMaxBatch];        // its number in the batch
+    uint32_t seq[kAttnMaxBatch / 4];   // its number in the batch, a byte each (words: scalar loads)
     // The stage copy a migrating launch carries (read only when it does):
     // logical blocks [mig_from, mig_to) of sequence mig_seq go to the blocks
     // mig_ids[j - mig_from] of the pool whose K and V bases dst_tab lists.
@@ -254,6 +254,64 @@ __device__ __forceinline__ uint32_t to16(float x)
     }
 }
 
+__device__ __forceinline__ uint32_t lds_offset(const void *p)
+{
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const void LLMIG_LDS *)p));
+}
+
+// A group's operands out of LDS: K fragment ks from k_at[ks], V^T fragment mt
+// from v_at + 32 * mt.  In assembly, with their wait, because the compiler
+// lets every LDS read wait for all outstanding loads into LDS and all stores
+// behind them (it cannot tell the group's from the ones still on their way).
+template <int KS, int MT>
+__device__ __forceinline__ void read_operands(const uint32_t *k_at, uint32_t v_at, u32x4 *kf, uint64_t *vf)
+{
+    if constexpr (KS == 4) {
+        asm volatile("ds_read_b128 %0, %12\n\t"
+                     "ds_read_b128 %1, %13\n\t"
+                     "ds_read_b128 %2, %14\n\t"
+                     "ds_read_b128 %3, %15\n\t"
+                     "ds_read_b64_tr_b16 %4, %16\n\t"
+                     "ds_read_b64_tr_b16 %5, %16 offset:32\n\t"
+                     "ds_read_b64_tr_b16 %6, %16 offset:64\n\t"
+                     "ds_read_b64_tr_b16 %7, %16 offset:96\n\t"
+                     "ds_read_b64_tr_b16 %8, %16 offset:128\n\t"
+                     "ds_read_b64_tr_b16 %9, %16 offset:160\n\t"
+                     "ds_read_b64_tr_b16 %10, %16 offset:192\n\t"
+                     "ds_read_b64_tr_b16 %11, %16 offset:224\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(vf[0]), "=&v"(vf[1]),
+                       "=&v"(vf[2]), "=&v"(vf[3]), "=&v"(vf[4]), "=&v"(vf[5]), "=&v"(vf[6]), "=&v"(vf[7])
+                     : "v"(k_at[0]), "v"(k_at[1]), "v"(k_at[2]), "v"(k_at[3]), "v"(v_at)
+                     : "memory");
+    } else {
+        static_assert(KS == 2 && MT == 4, "head_dim 64 or 128");
+        asm volatile("ds_read_b128 %0, %6\n\t"
+                     "ds_read_b128 %1, %7\n\t"
+                     "ds_read_b64_tr_b16 %2, %8\n\t"
+                     "ds_read_b64_tr_b16 %3, %8 offset:32\n\t"
+                     "ds_read_b64_tr_b16 %4, %8 offset:64\n\t"
+                     "ds_read_b64_tr_b16 %5, %8 offset:96\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(vf[0]), "=&v"(vf[1]), "=&v"(vf[2]), "=&v"(vf[3])
+                     : "v"(k_at[0]), "v"(k_at[1]), "v"(v_at)
+                     : "memory");
+    }
+}
+
+// Two KiB of K rows and two of V rows as the lanes loaded them.
+__device__ __forceinline__ void read_row_pair(uint32_t k_at, uint32_t v_at, u32x4 *k, u32x4 *v)
+{
+    asm volatile("ds_read_b128 %0, %4\n\t"
+                 "ds_read_b128 %1, %4 offset:1024\n\t"
+                 "ds_read_b128 %2, %5\n\t"
+                 "ds_read_b128 %3, %5 offset:1024\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(k[0]), "=&v"(k[1]), "=&v"(v[0]), "=&v"(v[1])
+                 : "v"(k_at), "v"(v_at)
+                 : "memory");
+}
+
 // Block ids a partition can touch, for the dynamic LDS of attn_partial_mfma
 // (UNITS 0): a partition may start inside a block, so at most
 // ceil(part_tokens / block_size) + 1 blocks.  A migrating launch keeps the
@@ -282,7 +340,7 @@ __host__ __device__ inline uint32_t attn_blk_slots(uint32_t part_tokens, uint32_
 // that never change).  A partition has at most 64 units per wavefront.  Other
 // block sizes stage the block ids in LDS and look each token's up.
 template <int BF16, int D, int MIG, int UNITS>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MIG ? 3 : 4, 8)))
 attn_partial_mfma(const AttnArgs a)
 {
     constexpr int KS = D / 32;            // k-steps of the QK product
@@ -342,7 +400,7 @@ attn_partial_mfma(const AttnArgs a)
     }
     const uint32_t item_first = s_lo > 0 ? a.item_end[s_lo - 1] : 0u;
     const uint32_t parts = a.item_end[s_lo] - item_first;
-    const uint32_t b = a.seq[s_lo];
+    const uint32_t b = (a.seq[s_lo / 4u] >> (8u * (s_lo % 4u))) & 0xffu;
     const int32_t ctx = a.ctx[s_lo];
     const int32_t plen = attn_part_len(ctx, parts);
     const int32_t start = static_cast<int32_t>(item - item_first) * plen;
@@ -470,7 +528,15 @@ attn_partial_mfma(const AttnArgs a)
     // that back and stores it where the chunk lives in the destination tile:
     // (slot of the token, head g, the chunk).  Rows of tokens past the
     // partition's end (loaded as copies of its last token) are skipped.
-    auto store_group = [&](int32_t tg) {
+    // Split in two, so that the next group's request goes out in between.
+    u32x4 rows_k[KS], rows_v[KS];
+    auto read_rows = [&]() {
+#pragma unroll
+        for (int j = 0; j < KS; j += 2)
+            read_row_pair(lds_offset(kbuf) + j * 1024 + lane * 16, lds_offset(vbuf) + j * 1024 + lane * 16, rows_k + j,
+                          rows_v + j);
+    };
+    auto store_rows = [&](int32_t tg) {
         // raw buffer stores over the destination layer tensors, with the
         // migration copy's cache policy (streaming, device scope); a whole
         // 10.7 GB stage carried by one GQA decode step added 2.2-2.8 ms to
@@ -484,7 +550,6 @@ attn_partial_mfma(const AttnArgs a)
         const __amdgpu_buffer_rsrc_t rv = tile_rsrc(
             reinterpret_cast<const uint8_t *>(table_entry(a.dst_tab, a.num_layers + layer)), a.dst_layer_bytes);
         uint32_t off[KS];
-        u32x4 r[KS];
         if constexpr (UNITS) {
             const uint32_t u0 = static_cast<uint32_t>(tg - tg0) / 32u;
 #pragma unroll
@@ -509,48 +574,61 @@ attn_partial_mfma(const AttnArgs a)
         }
 #pragma unroll
         for (int j = 0; j < KS; ++j)
-            r[j] = *reinterpret_cast<const u32x4 *>(kbuf + j * 1024 + lane * 16);
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+            buffer_store16(rk, off[j] + 16 * ((lane % LPR) ^ kswz(j * RPL + lane / LPR)), rows_k[j]);
 #pragma unroll
         for (int j = 0; j < KS; ++j)
-            buffer_store16(rk, off[j] + 16 * ((lane % LPR) ^ kswz(j * RPL + lane / LPR)), r[j]);
-#pragma unroll
-        for (int j = 0; j < KS; ++j)
-            r[j] = *reinterpret_cast<const u32x4 *>(vbuf + j * 1024 + lane * 16);
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-#pragma unroll
-        for (int j = 0; j < KS; ++j)
-            buffer_store16(rv, off[j] + 16 * (lane % LPR), r[j]);
+            buffer_store16(rv, off[j] + 16 * (lane % LPR), rows_v[j]);
+    };
+    // whether the group starting at token tg holds tokens of the stage's
+    // blocks (wavefront-uniform)
+    auto carries = [&](int32_t tg) {
+        return MIG && mig && (tg + 15) / bs >= a.mig_from && tg / bs < a.mig_to;
     };
     if (tg0 < end)
         request_group(tg0);
+    // K fragments (A operand): token r16, dims 32*ks + 8*g4 .. +8.  V^T
+    // fragments (A operand of O^T: dim 16*mt + r16, tokens 4*g4 .. +3) by
+    // transposing reads: lane r16 of the 16-lane group g4 receives element
+    // r16 % 4 of the 8 bytes that lane 4*q + r16/4 of its group addresses, for
+    // q = 0..3; those address token 4*g4 + q, dims 16*mt + 4*(r16 % 4) .. +3.
+    uint32_t k_at[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        k_at[ks] = lds_offset(kbuf) + r16 * RB + ((4 * ks + g4) ^ kswz(r16)) * 16;
+    const uint32_t v_at = lds_offset(vbuf) + (4 * g4 + r16 / 4) * RB + 4 * (r16 % 4) * 2;
+    // The query rows have landed too; said here, so that the compiler puts no
+    // wait for them, and with it for every store, into the loop.
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        asm volatile("" : "+v"(qf[ks]));
+    bool stored = false;    // the group before this one issued 2 * KS stores, after this one's request
     for (int32_t tg = tg0; tg < end; tg += 64) {
-        // this group's rows have landed (the only loads in flight)
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        // a migrating launch stores the stage's rows first, while no operand
-        // fragments are live yet; a group none of whose tokens lies in the
-        // stage's blocks skips it (a wavefront-uniform test)
-        if (MIG && mig && (tg + 15) / bs >= a.mig_from && tg / bs < a.mig_to)
-            store_group(tg);
-        // K fragments (A operand: token r16, dims 32*ks + 8*g4 .. +8)
+        // this group's rows have landed; loads and stores complete in order,
+        // so the stores behind them need not have
+        if (MIG && stored)
+            __builtin_amdgcn_s_waitcnt(kWaitVm0 | (2 * KS));
+        else
+            __builtin_amdgcn_s_waitcnt(kWaitVm0);
         u32x4 kf[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            kf[ks] = *reinterpret_cast<const u32x4 *>(kbuf + r16 * RB + (((4 * ks + g4) ^ kswz(r16)) * 16));
-        // V^T fragments (A operand of O^T: dim 16*mt + r16, tokens 4*g4 .. +3)
-        // by transposing reads: lane r16 of the 16-lane group g4 receives
-        // element r16 % 4 of the 8 bytes that lane 4*q + r16/4 of its group
-        // addresses, for q = 0..3; those address token 4*g4 + q, dims
-        // 16*mt + 4*(r16 % 4) .. +3.
         uint64_t vf[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            vf[mt] = __builtin_bit_cast(uint64_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (i16x4_t LLMIG_LDS *)(vbuf + (4 * g4 + r16 / 4) * RB + (16 * mt + 4 * (r16 % 4)) * 2)));
-        // the reads have returned before the next group's rows overwrite them
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        read_operands<KS, MT>(k_at, v_at, kf, vf);
+        const bool carry = carries(tg);
+        if (carry)
+            read_rows();
+        // (the reads have returned: the next group's rows may overwrite them)
         if (tg + 64 < end)
             request_group(tg + 64);
+        if (MIG) {
+            // the stores stay behind the request: the wait above counts on it
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            if (carry)
+                store_rows(tg);
+            stored = carry;
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // S^T = K . Q^T
         f32x4_t s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll

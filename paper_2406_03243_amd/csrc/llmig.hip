@@ -1189,7 +1189,7 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
         items += parts;
         a.item_end[s] = items;
         a.ctx[s] = ctx_lens[b];
-        a.seq[s] = static_cast<uint8_t>(b);
+        a.seq[s / 4] |= static_cast<uint32_t>(b) << (8 * (s % 4));
         if (parts > 1) {
             most = std::max(most, parts);
             r.seq_end[s] = items;
