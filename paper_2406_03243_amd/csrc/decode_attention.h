@@ -33,7 +33,8 @@ constexpr int kWaitVm0 = 0x0F70;
 constexpr int kWaitLgkm0 = 0xC07F;
 
 constexpr int kPartTokens = 2048;    // most tokens per partition
-constexpr int kMinPartTokens = 128;  // fewest tokens a sequence is split down to
+constexpr int kMinPartTokens = 256;  // fewest tokens a sequence is split down to
+constexpr int kWholeTokens = 512;    // a call of no longer sequences splits none
 constexpr int kAttnMaxBatch = 256;   // sequences per call (their partitions ride in the kernel arguments)
 // A partial result record: the partition's maximum score m (natural base),
 // its weight sum l, two floats of padding, then the D weighted V sums, so
@@ -57,7 +58,9 @@ struct AttnArgs {
     uint32_t part_tokens;       // most tokens of a partition in this call
     uint32_t item_end[kAttnMaxBatch];  // items of the first s + 1 sequences
     int32_t ctx[kAttnMaxBatch];        // tokens of sequence s
-    uint32_t seq[kAttnMaxBatch / 4];   // its number in the batch, a byte each (words: scalar loads)
+    // its number in the batch (low byte) and its partitions' length in 64
+    // tokens (high byte), 16 bits each (in words, for scalar loads)
+    uint32_t seq[kAttnMaxBatch / 2];
     // The stage copy a migrating launch carries (read only when it does):
     // logical blocks [mig_from, mig_to) of sequence mig_seq go to the blocks
     // mig_ids[j - mig_from] of the pool whose K and V bases dst_tab lists.
@@ -400,11 +403,11 @@ attn_partial_mfma(const AttnArgs a)
     }
     const uint32_t item_first = s_lo > 0 ? a.item_end[s_lo - 1] : 0u;
     const uint32_t parts = a.item_end[s_lo] - item_first;
-    const uint32_t b = (a.seq[s_lo / 4u] >> (8u * (s_lo % 4u))) & 0xffu;
-    const int32_t ctx = a.ctx[s_lo];
-    const int32_t plen = attn_part_len(ctx, parts);
+    const uint32_t seq = a.seq[s_lo / 2u] >> (16u * (s_lo % 2u));
+    const uint32_t b = seq & 0xffu;
+    const int32_t ctx = a.ctx[s_lo], plen = static_cast<int32_t>(seq >> 8 & 0xffu) * 64;
     const int32_t start = static_cast<int32_t>(item - item_first) * plen;
-    const int32_t end = min(ctx, start + plen);
+    const int32_t end = parts > 1 ? min(ctx, start + plen) : ctx;
     const uint32_t G = a.q_heads / a.kv_heads;
     const uint32_t wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     const uint32_t wv = uniform(wave);
@@ -454,17 +457,13 @@ attn_partial_mfma(const AttnArgs a)
         __syncthreads();
     }
 
-    // Q^T fragments (B operand): query row r16 of the group, dims 32*ks + 8*g4 .. +8.
+    // Q^T fragments (B operand): query row r16 of the group, dims 32*ks + 8*g4
+    // .. +8; rows past the group: the last one again, whose results go nowhere.
     u32x4 qf[KS];
+    const uint64_t q_row = (static_cast<uint64_t>(layer) * a.batch + b) * a.q_heads + g * G + min(r16, G - 1u);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        qf[ks] = u32x4{0u, 0u, 0u, 0u};
-        if (r16 < G) {
-            const uint64_t qoff = ((static_cast<uint64_t>(layer) * a.batch + b) * a.q_heads + g * G + r16) * D +
-                                  32 * ks + 8 * g4;
-            qf[ks] = load16(a.q + qoff * 2);
-        }
-    }
+    for (int ks = 0; ks < KS; ++ks)
+        qf[ks] = load16(a.q + (q_row * D + 32 * ks + 8 * g4) * 2);
     const float qk_scale = a.scale * kLog2e;
     float m = -INFINITY, lsum = 0.f;
     f32x4_t acc[MT];
@@ -780,8 +779,10 @@ inline int attn_record_bytes(const int32_t *ctx_lens, int32_t batch, int32_t par
 // work: shares of about kAttnWorkgroups workgroups, two a CU.  Measured, one
 // layer of 8 KV heads: one sequence of 32000 tokens, partitions of 2048 / 1024
 // / 512 / 256 tokens 42 / 28.6 / 30.1 / 31.9 us; three of up to 3000, 2048 /
-// 512 / 128 31.4 / 15.8 / 14.1 us; 32 layers of one sequence of 32000, 2048 /
-// 1024 / 512 703 / 729 / 773 us.  Records of a finer split stay within
+// 512 / 256 / 128 31.4 / 15.8 / 14.2 / 14.1 us; 32 layers of one sequence of 32000, 2048 /
+// 1024 / 512 703 / 729 / 773 us.  The merge is a launch of its own, so short
+// sequences stay whole (one of 300 tokens 10.9 us, in two 14.0; 80 layers of
+// one of 500 33 against 39).  Records of a finer split stay within
 // kSplitBytes, half of LLMIG_DECODE_SCRATCH_BYTES, so that every entry point
 // cuts a call alike.
 constexpr int64_t kAttnWorkgroups = 512;
@@ -791,9 +792,12 @@ inline int32_t attn_part_tokens(const int32_t *ctx_lens, int32_t batch, int64_t 
                                 int64_t q_heads, int64_t head_dim)
 {
     int64_t tokens = 0, work = 0;
-    for (int32_t b = 0; b < batch; ++b)
+    int32_t longest = 0;
+    for (int32_t b = 0; b < batch; ++b) {
         tokens += ctx_lens[b];
-    if (__builtin_mul_overflow(tokens, num_layers, &work) || __builtin_mul_overflow(work, kv_heads, &work) ||
+        longest = std::max(longest, ctx_lens[b]);
+    }
+    if (longest <= kWholeTokens || __builtin_mul_overflow(tokens, num_layers, &work) || __builtin_mul_overflow(work, kv_heads, &work) ||
         work >= kAttnWorkgroups * kPartTokens)
         return kPartTokens;
     int32_t part = static_cast<int32_t>((work / kAttnWorkgroups + 63) / 64 * 64);

@@ -1189,7 +1189,8 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
         items += parts;
         a.item_end[s] = items;
         a.ctx[s] = ctx_lens[b];
-        a.seq[s / 4] |= static_cast<uint32_t>(b) << (8 * (s % 4));
+        const uint32_t len64 = parts > 1 ? static_cast<uint32_t>(attn_part_len(ctx_lens[b], parts) / 64) : 0u;
+        a.seq[s / 2] |= (static_cast<uint32_t>(b) | len64 << 8) << (16 * (s % 2));
         if (parts > 1) {
             most = std::max(most, parts);
             r.seq_end[s] = items;
