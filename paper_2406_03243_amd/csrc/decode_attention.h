@@ -810,6 +810,17 @@ inline int32_t attn_part_tokens(const int32_t *ctx_lens, int32_t batch, int64_t 
     return part;
 }
 
+// Calls of long partitions leave some of the chip's workgroup slots empty, by
+// asking for LDS they don't use: with every slot taken more rows are in flight
+// than the memory system needs, and each workgroup's own waits (its start, its
+// end) last as long as that queue.  kLongPartLds leaves three workgroups a CU
+// for head_dim 128, four (of up to eight) for 64.  32 layers, head_dim 64, 32
+// heads, mean partition 860 / 1350 / 2048 tokens 137.9 -> 132.7, 170 -> 161,
+// 233 -> 223 us (600 tokens: level, 140: 99 -> 111); head_dim 128, 2000 tokens
+// 658 -> 651, 479 -> 472 (860 tokens: 270 -> 272).
+constexpr int64_t kLongPartTokens64 = 800, kLongPartTokens128 = 1500;
+constexpr size_t kLongPartLds = 15000;
+
 // The merge kernel for at most `most` partitions a sequence; returns its rows
 // per workgroup.
 inline uint32_t attn_reduce_kernel(int head_dim, uint32_t most, const void **fn)
