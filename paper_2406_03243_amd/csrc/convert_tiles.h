@@ -91,6 +91,7 @@ struct ConvertArgs {
     uint32_t pairs;             // pairs in this launch
     uint32_t units;             // slabs: pairs * 2 * num_layers * heads
     uint32_t first_unit;        // this launch's first slab (convert_slabs)
+    Divisor by_head, by_pair;   // division by heads and by pairs (not convert_tiles)
     uint32_t lin_first;         // this launch's first pair within the whole call
     uint32_t lin_pairs;         // pairs in the whole call (plane stride of the staging buffer)
     uint32_t first_slot;        // write_slabs: slot of the launch's first token in its block
@@ -214,9 +215,9 @@ __global__ void __launch_bounds__(WAVES * 64) convert_slabs(const ConvertArgs a)
     __shared__ u32x4 lds[68 * WAVES];                // 64 WAVES chunks + one pad per 16
     const uint32_t k = threadIdx.x;
     const uint32_t unit = a.first_unit + slab_of(blockIdx.x);
-    const uint32_t tile = unit / a.heads;
+    const uint32_t tile = divide(unit, a.by_head);
     const uint32_t h = unit - tile * a.heads;
-    const uint32_t plane = tile / a.pairs;
+    const uint32_t plane = divide(tile, a.by_pair);
     const uint32_t i = tile - plane * a.pairs;
     const uint32_t layer = plane >> 1, kv = plane & 1u;
     const int32_t sl = a.layouts[kv], dl = a.layouts[2 + kv];
@@ -261,9 +262,9 @@ __global__ void __launch_bounds__(WAVES * 64) write_slabs(const ConvertArgs a)
     __shared__ u32x4 lds[68 * WAVES];
     const uint32_t k = threadIdx.x;
     const uint32_t unit = a.first_unit + slab_of(blockIdx.x);
-    const uint32_t tile = unit / a.heads;
+    const uint32_t tile = divide(unit, a.by_head);
     const uint32_t h = unit - tile * a.heads;
-    const uint32_t plane = tile / a.pairs;
+    const uint32_t plane = divide(tile, a.by_pair);
     const uint32_t i = tile - plane * a.pairs;
     const uint32_t layer = plane >> 1, kv = plane & 1u;
     const int32_t dl = a.layouts[2 + kv];
@@ -448,6 +449,7 @@ void convert_magic(ConvertArgs &a)
     a.magic_row = magic_for(a.row_chunks);
     a.magic_bs = magic_for(a.block_size);
     a.magic_t = magic_for(a.t_chunks > 0 ? a.t_chunks : 1u);
+    a.by_head = divisor(a.heads);
 }
 
 // Chunks per lane (a power of two) for slabs of `chunks` 16-byte chunks.
@@ -498,6 +500,7 @@ int launch_convert(ConvertArgs a, const int32_t *src_ids, const int32_t *dst_ids
     for (int64_t first = 0; first < n; first += static_cast<int64_t>(per_launch)) {
         const uint32_t m = static_cast<uint32_t>(std::min<int64_t>(n - first, per_launch));
         a.pairs = m;
+        a.by_pair = divisor(m);
         a.units = static_cast<uint32_t>(m * units_per_pair);
         a.lin_first = static_cast<uint32_t>(first);
         if (ids == kIdsDevice) {

@@ -109,6 +109,7 @@ struct CopyArgs {
     uint32_t spans_per_tile;
     uint32_t items;             // wave items: pairs * planes * spans_per_tile
     uint32_t first_item;        // this launch's first item (copy_rows)
+    Divisor by_span, by_pair;   // division by spans_per_tile and by pairs (copy_rows)
     uint32_t xcd_runs;          // copy_rows: 1 if each XCD takes runs of kXcdRun items
     uint32_t lin_first;         // this launch's first pair within the whole call
     uint32_t lin_pairs;         // pairs in the whole call
@@ -158,9 +159,9 @@ __global__ void __launch_bounds__(64) copy_rows(const CopyArgs a)
             w = round * (8u * kXcdRun) + (r % 8u) * kXcdRun + r / 8u;
     }
     const uint32_t item = a.first_item + w;
-    const uint32_t tile = item / a.spans_per_tile;
+    const uint32_t tile = divide(item, a.by_span);
     const uint32_t span = item - tile * a.spans_per_tile;
-    const uint32_t plane = tile / a.pairs;      // layer * 2 + kv
+    const uint32_t plane = divide(tile, a.by_pair);     // layer * 2 + kv
     const uint32_t i = tile - plane * a.pairs;
     const uint32_t layer = plane >> 1, kv = plane & 1u;
 
@@ -313,6 +314,7 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
         span = 2;
     }
     a.spans_per_tile = spans(span);
+    a.by_span = divisor(a.spans_per_tile);
     const uint64_t items_per_pair = planes * a.spans_per_tile;
     const uint64_t per_launch = std::min<uint64_t>(0x7fffffffull / items_per_pair,
                                                    ids_on_device ? UINT64_MAX : static_cast<uint64_t>(inline_pairs));
@@ -336,6 +338,7 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
     for (int64_t first = 0; first < n; first += static_cast<int64_t>(per_launch)) {
         const uint32_t m = static_cast<uint32_t>(std::min<int64_t>(n - first, per_launch));
         a.pairs = m;
+        a.by_pair = divisor(m);
         a.lin_first = static_cast<uint32_t>(first);
         a.items = static_cast<uint32_t>(m * items_per_pair);
         if (ids == kIdsDevice) {

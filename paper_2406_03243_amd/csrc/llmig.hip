@@ -93,6 +93,7 @@ struct WriteArgs {
     uint32_t blocks;       // blocks this launch touches
     uint32_t rows_per_run; // write_rows: KiB of the longest run of a block's tokens
     uint32_t first_item;   // write_rows: this launch's first KiB
+    Divisor by_row, by_block; // write_rows: division by rows_per_run and by blocks
     int32_t ids[kInlinePairs]; // blocks this launch touches, in logical order
 };
 
@@ -143,9 +144,9 @@ __global__ void __launch_bounds__(kThreads) write_token_slots(const WriteArgs a)
 __global__ void __launch_bounds__(64) write_rows(const WriteArgs a)
 {
     const uint32_t item = a.first_item + blockIdx.x;
-    const uint32_t run = item / a.rows_per_run;
+    const uint32_t run = divide(item, a.by_row);
     const uint32_t row = item - run * a.rows_per_run;
-    const uint32_t plane = run / a.blocks;
+    const uint32_t plane = divide(run, a.by_block);
     const uint32_t i = run - plane * a.blocks;
     const uint32_t layer = plane >> 1, kv = plane & 1u;
     const uint32_t lo = i == 0 ? a.first_slot : 0u;
@@ -1017,6 +1018,7 @@ int llmig_write_tokens(const llmig_pool *pool, const int32_t *table, int64_t tab
             c.tokens = a.tokens;
             c.lin_first = a.first_token;
             c.pairs = static_cast<uint32_t>(nblk);
+            c.by_pair = divisor(c.pairs);
             std::memcpy(c.ids, table + blk0, static_cast<size_t>(nblk) * sizeof(int32_t));
             const uint32_t threads = (c.chunks + 63u) / 64u * 64u;
             const uint64_t units = static_cast<uint64_t>(nblk) * 2 * c.num_layers * c.heads;
@@ -1034,6 +1036,8 @@ int llmig_write_tokens(const llmig_pool *pool, const int32_t *table, int64_t tab
             void *args[] = {&a};
             if (rows) {
                 a.rows_per_run = static_cast<uint32_t>((std::min<int64_t>(bs, a.tokens) * slot_bytes + 1023) / 1024);
+                a.by_row = divisor(a.rows_per_run);
+                a.by_block = divisor(a.blocks);
                 const uint64_t items = static_cast<uint64_t>(nblk) * 2 * a.num_layers * a.rows_per_run;
                 for (uint64_t at = 0; at < items && e == hipSuccess; at += kMaxRowsPerLaunch) {
                     a.first_item = static_cast<uint32_t>(at);
