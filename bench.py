@@ -53,7 +53,7 @@ def recorded_traffic(kernel: str):
     """HBM bytes per launch of ``kernel`` from the committed counter summary
     (two rocprofv3 --pmc passes, calibrated against a plain copy), or None
     when the kernel source has changed since the counters were taken."""
-    path = os.path.join(ROOT, "profiles", "copy_tiles_bulk_llama7b_traffic.txt")
+    path = os.path.join(ROOT, "profiles", "copy_rows_llama7b_traffic.txt")
     try:
         rec = json.load(open(path))
         now = copy_kernel_hash()
