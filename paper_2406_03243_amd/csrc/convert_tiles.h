@@ -23,7 +23,7 @@
 //    1 KiB and the slabs run plane by plane over pairs sorted by destination
 //    block.  Against the kernel below (a slab per wavefront, 4 chunks a lane,
 //    pair by pair) on MI355X: 32 heads of 16 x 128, token-major to head-major
-//    6.33 -> 6.75 TB/s, to HCNX/HDN 6.28 -> 6.49, back 6.04 -> 6.59; 8 heads
+//    6.33 -> 6.75 TB/s, to HCNX/HDN 6.28 -> 6.68, back 6.04 -> 6.59; 8 heads
 //    4.95 -> 6.49, 4.93 -> 6.15, 4.94 -> 6.30; one head 4.67 -> 6.06,
 //    4.64 -> 5.63, 4.63 -> 5.78.
 //  * Each XCD takes runs of kSlabRun = 64 slabs, so that the slabs of one

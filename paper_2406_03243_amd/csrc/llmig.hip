@@ -74,7 +74,7 @@ namespace {
 //    a time).
 // Measured on MI355X against write_token_slots alone, 2000 tokens, 32 layers
 // of 32 heads of 128: token-major 380 -> 315 us (6.7 TB/s read + written),
-// head-major 393 -> 319, HCNX keys and HDN values 2221 -> 325; one head 78 ->
+// head-major 393 -> 319, HCNX keys and HDN values 2221 -> 320; one head 78 ->
 // 11.7, 79 -> 12.2, 97 -> 12.8.
 struct WriteArgs {
     const uint64_t *tab;
