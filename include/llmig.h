@@ -369,7 +369,8 @@ int llmig_stream_read(const void *region, int64_t bytes, int32_t passes, int32_t
  * fp16, 1 bf16), 16-byte aligned; tables device int32, ids the caller
  * guarantees in range; ctx_lens a HOST array; out device float32
  * [num_layers][batch][q_heads][head_dim], 16-byte aligned; a sequence of
- * length 0 gives zeros.  workspace: device memory of the size
+ * length 0 gives zeros, and so does a row whose scores hold a NaN or +inf or
+ * are all -inf (a score of -inf is a weight of 0).  workspace: device memory of the size
  * llmig_decode_attention_workspace returns for the same lengths, 16-byte
  * aligned.  (That size lets a small call be cut finely enough to use the
  * whole chip.  A call also takes any size that holds, per layer and query

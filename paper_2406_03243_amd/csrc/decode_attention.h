@@ -118,8 +118,10 @@ __global__ void __launch_bounds__(kThreads) attn_reduce(const AttnReduceArgs a)
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     auto merge = [&](float m2, float l2, float4 v) {
         const float mm = fmaxf(m, m2);
-        if (mm == -INFINITY)
+        if (mm == -INFINITY) {      // no weight on either side; a NaN sum stays one
+            l += l2;
             return;
+        }
         const float c1 = __expf(m - mm), c2 = __expf(m2 - mm);
         l = l * c1 + l2 * c2;
         acc.x = acc.x * c1 + v.x * c2;
@@ -642,12 +644,14 @@ attn_partial_mfma(const AttnArgs a)
         }
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m, mx);          // finite: the group has a valid token
-        const float c = exp2f(m - m_new);
+        // A maximum of -inf (every score so far is) must not be subtracted:
+        // where a partition starts decides what "so far" holds.
+        const float m_new = fmaxf(m, mx), m_sub = m_new == -INFINITY ? 0.f : m_new;
+        const float c = exp2f(m - m_sub);
         float p[4], ps = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            p[i] = exp2f(sc[i] - m_new);
+            p[i] = exp2f(sc[i] - m_sub);
             ps += p[i];
         }
         ps += __shfl_xor(ps, 16);
@@ -713,8 +717,8 @@ attn_partial_mfma(const AttnArgs a)
             ll += sh_l[w][row] * c;
             o += *reinterpret_cast<const f32x4_t *>(so + (w * 16 + row) * kMergeRow + 4 * d4) * c;
         }
-        if (whole && ll > 0.f)
-            o = o / ll;
+        if (whole)                  // as the merge kernel: zeros where there is no finite weight sum
+            o = ll > 0.f ? o / ll : f32x4_t{0.f, 0.f, 0.f, 0.f};
         put(row * out_row + out_at + 4 * d4, o);
         // the reduce kernel merges with natural exponentials: m in that base
         if (!whole && d4 == 0)
