@@ -146,38 +146,51 @@ __device__ __forceinline__ void buffer_store16(__amdgpu_buffer_rsrc_t r, uint32_
     __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kStreamStore);
 }
 
-// Calls of fewer pairs keep the caller's order (too few to be neighbours).
+// Whether a copy of n pairs of pair_bytes bytes each (one way, all layers, K
+// and V) is worth ordering by destination on the host before its first launch.
+// Ordering takes 2-4 ns a pair and delays that launch, so the copy of a pair
+// must take longer, 20 ns from 64 KiB on; and the call must be longer than
+// the queue of one launch, or DRAM has no order to see.  Measured, read +
+// written: 24 MB of 366 pairs 10.6 us in the caller's order, 11.7 ordered; 48
+// MB of 183 10.5 and 11.3; 64 MB level; 96 MB of 732 22.0 and 21.0; 170 MB of
+// 400 29.8 and 28.2; 16 KiB a pair, 12000 pairs level, and up to 13% slower
+// where the call has the GPU to itself; 64 KiB a pair, 12000 pairs 368 and 320.
 constexpr int64_t kSortPairs = 32;
+constexpr uint64_t kSortPairBytes = 64 << 10, kSortCallBytes = 48 << 20;
 
-// Sorts the pairs of a call by destination id: out[k] = (source, destination)
-// as one word, source in the low half.  src null: the source of pair k is k.
-// A least-significant-digit radix sort, 11 bits a pass (two passes for 16-bit
-// ids), which leaves 512 pairs sorted in 2-3 us.
-void sort_pairs(const int32_t *src, const int32_t *dst, int64_t n, std::vector<uint64_t> &out)
+inline bool ordering_pays(int64_t n, uint64_t pair_bytes)
+{
+    return n >= kSortPairs && pair_bytes >= kSortPairBytes &&
+           static_cast<uint64_t>(n) >= (kSortCallBytes + pair_bytes - 1) / pair_bytes;
+}
+
+// Orders the pairs of a call by the leading 11 bits of their destination ids
+// (of the largest one's bits): out[k] = (source, destination) as one word,
+// source in the low half.  src null: the source of pair k is k.  One counting
+// pass, as fast to copy in as a full sort (which took two or three), and
+// 5-10% sooner enqueued for calls of thousands of pairs.
+void order_pairs(const int32_t *src, const int32_t *dst, int64_t n, std::vector<uint64_t> &out)
 {
     constexpr int kBits = 11;
-    constexpr uint32_t kMask = (1u << kBits) - 1;
-    std::vector<uint64_t> tmp(static_cast<size_t>(n));
     out.resize(static_cast<size_t>(n));
-    uint32_t hi = 0;
-    for (int64_t k = 0; k < n; ++k) {
-        hi |= static_cast<uint32_t>(dst[k]);
-        out[static_cast<size_t>(k)] = static_cast<uint64_t>(static_cast<uint32_t>(dst[k])) << 32 |
-                                      static_cast<uint32_t>(src ? src[k] : static_cast<int32_t>(k));
+    uint32_t all = 0;
+    for (int64_t k = 0; k < n; ++k)
+        all |= static_cast<uint32_t>(dst[k]);
+    int shift = 0;
+    while ((all >> shift) >> kBits)
+        ++shift;
+    uint32_t at[1u << kBits] = {};
+    for (int64_t k = 0; k < n; ++k)
+        ++at[static_cast<uint32_t>(dst[k]) >> shift];
+    uint32_t sum = 0;
+    for (uint32_t &c : at) {
+        const uint32_t here = c;
+        c = sum;
+        sum += here;
     }
-    for (int shift = 0; shift < 32 && (hi >> shift) != 0; shift += kBits) {
-        uint32_t at[kMask + 1] = {};
-        for (uint64_t v : out)
-            ++at[static_cast<uint32_t>(v >> (32 + shift)) & kMask];
-        uint32_t sum = 0;
-        for (uint32_t &c : at) {
-            const uint32_t here = c;
-            c = sum;
-            sum += here;
-        }
-        for (uint64_t v : out)
-            tmp[at[static_cast<uint32_t>(v >> (32 + shift)) & kMask]++] = v;
-        out.swap(tmp);
+    for (int64_t k = 0; k < n; ++k) {
+        const uint32_t d = static_cast<uint32_t>(dst[k]);
+        out[at[d >> shift]++] = static_cast<uint64_t>(d) << 32 | static_cast<uint32_t>(src ? src[k] : static_cast<int32_t>(k));
     }
 }
 
@@ -185,14 +198,14 @@ void sort_pairs(const int32_t *src, const int32_t *dst, int64_t n, std::vector<u
 // null (a staging source): the pair's place in the call takes its place;
 // dst null (a staging destination): none.
 inline void inline_ids(uint32_t *ids, int mode, const int32_t *src, const int32_t *dst,
-                       const std::vector<uint64_t> &sorted, int64_t first, uint32_t m)
+                       const std::vector<uint64_t> &ordered, int64_t first, uint32_t m)
 {
     for (uint32_t k = 0; k < m; ++k) {
         const int64_t j = first + k;
         uint32_t s, d;
-        if (!sorted.empty()) {
-            s = static_cast<uint32_t>(sorted[static_cast<size_t>(j)]);
-            d = static_cast<uint32_t>(sorted[static_cast<size_t>(j)] >> 32);
+        if (!ordered.empty()) {
+            s = static_cast<uint32_t>(ordered[static_cast<size_t>(j)]);
+            d = static_cast<uint32_t>(ordered[static_cast<size_t>(j)] >> 32);
         } else {
             s = static_cast<uint32_t>(src ? src[j] : static_cast<int32_t>(j));
             d = dst ? static_cast<uint32_t>(dst[j]) : 0u;

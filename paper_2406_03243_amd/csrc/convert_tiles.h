@@ -20,8 +20,8 @@
 //  * convert_slabs, every uncapped launch: one workgroup per slab, one
 //    16-byte chunk per lane.  As in the same-layout copy, what bounds it is
 //    HBM and the DRAM order of the bytes in flight, so each wavefront moves
-//    1 KiB and the slabs run plane by plane over pairs sorted by destination
-//    block.  Against the kernel below (a slab per wavefront, 4 chunks a lane,
+//    1 KiB and the slabs run plane by plane over pairs ordered by destination
+//    block (order_pairs).  Against the kernel below (a slab per wavefront, 4 chunks a lane,
 //    pair by pair) on MI355X: 32 heads of 16 x 128, token-major to head-major
 //    6.33 -> 6.75 TB/s, to HCNX/HDN 6.28 -> 6.68, back 6.04 -> 6.59; 8 heads
 //    4.95 -> 6.49, 4.93 -> 6.15, 4.94 -> 6.30; one head 4.67 -> 6.06,
@@ -483,12 +483,12 @@ int launch_convert(ConvertArgs a, const int32_t *src_ids, const int32_t *dst_ids
                                                    ids_on_device ? UINT64_MAX : inline_pairs);
     if (per_launch == 0)
         return LLMIG_EINVAL;
-    std::vector<uint64_t> sorted;
-    if (!capped && !ids_on_device && n >= kSortPairs) {
+    std::vector<uint64_t> ordered;
+    if (!capped && !ids_on_device && ordering_pays(n, 2ull * a.num_layers * a.tile_bytes)) {
         try {
-            sort_pairs(src_ids, dst_ids, n, sorted);
+            order_pairs(src_ids, dst_ids, n, ordered);
         } catch (...) {
-            sorted.clear();     // no memory for it: the caller's order
+            ordered.clear();    // no memory for it: the caller's order
         }
     }
     const void *fn = convert_kernel(ids, per_lane, capped);
@@ -507,7 +507,7 @@ int launch_convert(ConvertArgs a, const int32_t *src_ids, const int32_t *dst_ids
             a.src_ids_dev = src_ids ? src_ids + first : nullptr;
             a.dst_ids_dev = dst_ids + first;
         } else {
-            inline_ids(a.ids, ids, src_ids, dst_ids, sorted, first, m);
+            inline_ids(a.ids, ids, src_ids, dst_ids, ordered, first, m);
         }
         void *args[] = {&a};
         const bool last_pairs = first + static_cast<int64_t>(per_launch) >= n;

@@ -25,11 +25,12 @@
 //  * The order is plane-major: all pairs of one (layer, K/V) tensor, then
 //    the next tensor.  Pair-major order spreads neighbouring rows over 2 *
 //    num_layers tensors (4 KiB tiles: 5.0 against 5.9-6.3 TB/s).
-//  * The pairs of a bulk launch with ids on the host are sorted by
-//    destination block, so that the writes of a tensor sweep it upwards:
-//    +2-9% over random pairs on tiles up to 64 KiB, +1% on 128 KiB (sorting
-//    by source instead gains half of that or less).  The order of the pairs
-//    is free: no destination block occurs twice in a call.
+//  * The pairs of a bulk call with ids on the host are ordered by destination
+//    block (order_pairs), so that the writes of a tensor sweep it upwards:
+//    +2-9% over random pairs on tiles up to 64 KiB, +1% on 128 KiB (ordering
+//    by source instead gains half of that or less; ordering launch by launch
+//    of 512 pairs loses half of it from 2000 pairs on).  The order is free: no
+//    destination block occurs twice in a call.
 //  * Consecutive rows go to the eight XCDs in turn, the dispatcher's own
 //    order, for tiles below 128 KiB; from there on each XCD takes runs of
 //    kXcdRun rows (128 KiB tiles 6.63 -> 6.84, 256 KiB 6.75 -> 6.81, but
@@ -97,7 +98,7 @@ enum Side { kPool = 0, kLinear = 1 };
 // tab[kv * L + l] + id * tile_bytes; linear sides address tile x of plane
 // (l, kv) at lin + ((l * 2 + kv) * lin_pairs + x) * tile_bytes.  For pair i
 // of the launch, x is lin_first + i, or, for a linear source whose pairs
-// were sorted, the pair's place in the call, which then rides as its source
+// were reordered, the pair's place in the call, which then rides as its source
 // id (kIds32).
 struct CopyArgs {
     const uint64_t *src_tab;
@@ -326,12 +327,12 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
                                                    ids_on_device ? UINT64_MAX : static_cast<uint64_t>(inline_pairs));
     if (per_launch == 0)
         return LLMIG_EINVAL;
-    std::vector<uint64_t> sorted;
-    if (!capped && span == 1 && DST == kPool && ids != kIdsDevice && n >= kSortPairs) {
+    std::vector<uint64_t> ordered;
+    if (!capped && DST == kPool && ids != kIdsDevice && ordering_pays(n, planes * a.tile_bytes)) {
         try {
-            sort_pairs(src_ids, dst_ids, n, sorted);
+            order_pairs(src_ids, dst_ids, n, ordered);
         } catch (...) {
-            sorted.clear();     // no memory for it: the caller's order
+            ordered.clear();    // no memory for it: the caller's order
         }
     }
     a.lin_pairs = static_cast<uint32_t>(n);
@@ -351,7 +352,7 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
             a.src_ids_dev = src_ids ? src_ids + first : nullptr;
             a.dst_ids_dev = dst_ids ? dst_ids + first : nullptr;
         } else {
-            inline_ids(a.ids, ids, src_ids, dst_ids, sorted, first, m);
+            inline_ids(a.ids, ids, src_ids, dst_ids, ordered, first, m);
         }
         void *args[] = {&a};
         const bool last_pairs = first + static_cast<int64_t>(per_launch) >= n;

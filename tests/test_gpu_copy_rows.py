@@ -1,10 +1,10 @@
 """The uncapped tile copy (one 1 KiB row per wavefront) where its dispatch
 turns, byte for byte against the CPU oracle: launches on both sides of the
 small-launch rule, on both sides of the rule that hands each XCD runs of rows
-(whole rounds, a ragged tail, less than one round), pairs sorted by
-destination or too few to be sorted, 16-bit, 32-bit and device ids, several
+(whole rounds, a ragged tail, less than one round), pairs in the caller's
+order and pairs ordered by destination, 16-bit, 32-bit and device ids, several
 launches, tiles that are not whole rows, and staging buffers on either side
-(where sorted pairs carry their place in the buffer)."""
+(where reordered pairs carry their place in the buffer)."""
 import sys
 
 import numpy as np
@@ -24,14 +24,16 @@ if torch.cuda.is_available():
 
 # layers, blocks, block_size, heads, head_dim, pairs
 CASES = [
-    (1, 40, 16, 32, 128, 31),       # 7936 rows: the small launch; pairs not sorted; under one round of runs
+    (1, 40, 16, 32, 128, 31),       # 7936 rows: the small launch; under one round of runs
     (1, 40, 16, 32, 128, 32),       # 8192 rows: the last small launch
-    (1, 40, 16, 32, 128, 33),       # 8448 rows: sorted, two whole rounds and a tail
+    (1, 40, 16, 32, 128, 33),       # 8448 rows: two whole rounds and a tail
     (2, 200, 16, 33, 128, 61),      # 132 KiB tiles: runs that cross tiles, a ragged tail
     (1, 80, 16, 31, 128, 70),       # 124 KiB tiles: rows dealt in turn
     (3, 700, 16, 3, 64, 600),       # 6 KiB tiles, 512 + 88 pairs
     (2, 1500, 8, 5, 40, 1100),      # 3200-byte tiles: a partial last row, three launches
     (1, 66000, 1, 1, 24, 9000),     # 48-byte tiles, ids past 16 bits
+    (1, 220, 16, 32, 128, 200),     # 50 MiB: ordered by destination
+    (2, 2500, 16, 4, 128, 1000),    # ordered, ids past 11 bits, several launches
 ]
 
 
@@ -81,15 +83,16 @@ def test_copy_rows(case, dev):
     assert image(dst).equals(hd), "unpack differs"
 
 
-# converting stages of more than one round of XCD runs, sorted pairs, slabs of
-# 1 to 16 wavefronts: layers, blocks, block_size, heads, head_dim, pairs
+# converting stages of more than one round of XCD runs, slabs of 1 to 16
+# wavefronts: layers, blocks, block_size, heads, head_dim, pairs
 CONVERT_CASES = [
     (1, 60, 8, 3, 64, 50),          # 1 KiB slabs
     (2, 80, 16, 5, 40, 70),         # 80 chunks: a partial second wavefront
     (1, 40, 16, 13, 128, 33),       # 858 slabs: one round of runs and a tail
-    (1, 40, 32, 9, 128, 31),        # 8 KiB slabs, too few pairs to sort
+    (1, 40, 32, 9, 128, 31),        # 8 KiB slabs
     (1, 34, 64, 2, 128, 34),        # 16 KiB slabs
     (1, 600, 8, 2, 16, 530),        # 256-byte slabs, two launches
+    (1, 1000, 16, 16, 128, 500),    # ordered by destination
 ]
 
 
