@@ -35,15 +35,16 @@
 //    order, for tiles below 128 KiB; from there on each XCD takes runs of
 //    kXcdRun rows (128 KiB tiles 6.63 -> 6.84, 256 KiB 6.75 -> 6.81, but
 //    64 KiB 6.69 -> 6.66 and 32 KiB 6.66 -> 6.44 TB/s).
-//  * A pool-to-pool launch of at most one round of resident wavefronts (a
-//    final stage of a block or so) moves two rows per wavefront: it has no
-//    DRAM order to keep, and half as many wavefronts to dispatch (one block of
-//    60 layers of 52 KiB tiles 4.87 against 5.10 us, of 80 layers of 32 KiB
-//    4.27 against 4.63 us, of 32 layers of 128 KiB 5.03 against 5.09 us).  A
-//    copy to or from a staging buffer keeps one row: over the host link two
-//    were 1-3% slower (six pieces of 2.6 MB of 128 KiB tiles each way 723
-//    against 702 us, one of 3.9 MB of 16 KiB tiles 216 against 210 us), beside
-//    a staging buffer in HBM they make no difference.
+//  * A launch of at most one round of resident wavefronts (a final stage of
+//    a block or so) moves two rows per wavefront: it has no DRAM order to
+//    keep, and half as many wavefronts to dispatch (one block of 60 layers of
+//    52 KiB tiles 4.87 against 5.10 us, of 80 layers of 32 KiB 4.27 against
+//    4.63 us, of 32 layers of 128 KiB 5.03 against 5.09 us; 4000 pairs of 2 KiB
+//    tiles of 2 layers through a staging buffer in HBM, 32 launches, 106
+//    against 110 us).  With the staging buffer in host memory it keeps one:
+//    two were 1-3% slower over the link (six pieces of 2.6 MB of 128 KiB tiles
+//    each way 723 against 702 us, one of 3.9 MB of 16 KiB tiles 216 against
+//    210 us).
 //
 // copy_tiles, launches under a workgroup cap (the throttle of a migration's
 // non-final stages).  Few resident workgroups walk the items, so each must
@@ -272,10 +273,8 @@ const void *copy_kernel_span(int span)
 template <int SRC, int DST, int IDS>
 const void *copy_kernel_rows(int rows)
 {
-    if constexpr (SRC == kPool && DST == kPool)
-        if (rows == 2)
-            return reinterpret_cast<const void *>(&copy_rows<SRC, DST, IDS, 2>);
-    return reinterpret_cast<const void *>(&copy_rows<SRC, DST, IDS, 1>);
+    return rows == 2 ? reinterpret_cast<const void *>(&copy_rows<SRC, DST, IDS, 2>)
+                     : reinterpret_cast<const void *>(&copy_rows<SRC, DST, IDS, 1>);
 }
 
 template <int SRC, int DST>
@@ -300,11 +299,11 @@ constexpr uint32_t kMaxRowsPerLaunch = 1u << 24;
 // max_workgroups > 0 caps the grid (pool to pool with host ids only): fewer,
 // resident workgroups walk the items, leaving the rest of the chip (and of
 // HBM) to other work.  ids16: every id of both lists is below 65536 (pool to
-// pool only).  Throws nothing.
+// pool only).  host_staging: the linear side is host memory.  Throws nothing.
 template <int SRC, int DST>
 int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int64_t n,
                 bool ids_on_device, hipStream_t stream, uint32_t max_workgroups = 0, bool ids16 = false,
-                const LaunchEvents &ev = LaunchEvents())
+                const LaunchEvents &ev = LaunchEvents(), bool host_staging = false)
 {
     const int ids = ids_on_device ? kIdsDevice : (SRC == kPool && DST == kPool && ids16) ? kIds16 : kIds32;
     const int64_t inline_pairs = ids == kIds16 ? 2 * kInlinePairs : kInlinePairs;
@@ -317,7 +316,7 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
         span = bulk_span(a.tile_bytes);
         if (pairs_first_launch * planes * spans(span) < kBulkWaveItemsPerCU * compute_units())
             span = 2;
-    } else if (SRC == kPool && DST == kPool && pairs_first_launch * planes * spans(1) <= kWavesPerCU * compute_units()) {
+    } else if (!host_staging && pairs_first_launch * planes * spans(1) <= kWavesPerCU * compute_units()) {
         span = 2;
     }
     a.spans_per_tile = spans(span);

@@ -412,8 +412,9 @@ bool has_repeat_any(const int32_t *ids, int64_t n)
 }
 
 // Device-visible address of a staging buffer: device memory as is, pinned
-// host memory through its device mapping.  Pageable memory is refused.
-int staging_pointer(const void *p, void **out)
+// host memory through its device mapping (*on_host).  Pageable memory is
+// refused.
+int staging_pointer(const void *p, void **out, bool *on_host)
 {
     hipPointerAttribute_t attr;
     std::memset(&attr, 0, sizeof(attr));
@@ -422,6 +423,7 @@ int staging_pointer(const void *p, void **out)
         (void)hipGetLastError();
         return LLMIG_EINVAL;
     }
+    *on_host = attr.type == hipMemoryTypeHost;
     if (attr.type == hipMemoryTypeDevice) {
         *out = const_cast<void *>(p);
         return LLMIG_OK;
@@ -889,7 +891,8 @@ int llmig_pack(const llmig_pool *src, const int32_t *blocks, int64_t n, int map_
         if (rc != LLMIG_OK || n == 0)
             return rc;
         void *lin = nullptr;
-        rc = staging_pointer(staging, &lin);
+        bool on_host = false;
+        rc = staging_pointer(staging, &lin, &on_host);
         if (rc != LLMIG_OK)
             return rc;
         CopyArgs a;
@@ -898,8 +901,8 @@ int llmig_pack(const llmig_pool *src, const int32_t *blocks, int64_t n, int map_
         a.dst_lin = static_cast<uint8_t *>(lin);
         a.tile_bytes = static_cast<uint32_t>(src->tile_bytes);
         a.num_layers = static_cast<uint32_t>(src->num_layers);
-        return launch_copy<kPool, kLinear>(a, blocks, nullptr, n, map_on_device != 0,
-                                           static_cast<hipStream_t>(stream));
+        return launch_copy<kPool, kLinear>(a, blocks, nullptr, n, map_on_device != 0, static_cast<hipStream_t>(stream),
+                                           0, false, LaunchEvents(), on_host);
     });
 }
 
@@ -911,7 +914,8 @@ int llmig_unpack(const llmig_pool *dst, const int32_t *blocks, int64_t n, int ma
         if (rc != LLMIG_OK || n == 0)
             return rc;
         void *lin = nullptr;
-        rc = staging_pointer(staging, &lin);
+        bool on_host = false;
+        rc = staging_pointer(staging, &lin, &on_host);
         if (rc != LLMIG_OK)
             return rc;
         CopyArgs a;
@@ -920,8 +924,8 @@ int llmig_unpack(const llmig_pool *dst, const int32_t *blocks, int64_t n, int ma
         a.src_lin = static_cast<const uint8_t *>(lin);
         a.tile_bytes = static_cast<uint32_t>(dst->tile_bytes);
         a.num_layers = static_cast<uint32_t>(dst->num_layers);
-        return launch_copy<kLinear, kPool>(a, nullptr, blocks, n, map_on_device != 0,
-                                           static_cast<hipStream_t>(stream));
+        return launch_copy<kLinear, kPool>(a, nullptr, blocks, n, map_on_device != 0, static_cast<hipStream_t>(stream),
+                                           0, false, LaunchEvents(), on_host);
     });
 }
 
@@ -944,7 +948,8 @@ int llmig_unpack_layout(const llmig_pool *dst, const int32_t *blocks, int64_t n,
         if (n == 0)
             return LLMIG_OK;
         void *lin = nullptr;
-        rc = staging_pointer(staging, &lin);
+        bool on_host = false;
+        rc = staging_pointer(staging, &lin, &on_host);
         if (rc != LLMIG_OK)
             return rc;
         ConvertArgs c = convert_args(dst, from, dst->layouts);

@@ -36,9 +36,9 @@ SMALL, LARGE = (4, 2000, 16, 2, 128), (11, 64, 32, 8, 128)
 
 @pytest.mark.parametrize("call", ["pack", "unpack"])
 @pytest.mark.parametrize("pool", [SMALL, LARGE], ids=["8KiB", "64KiB"])
-def test_staging_copies_move_one_row_a_wavefront(record, call, pool):
-    """Few rows or many, a copy to or from a staging buffer takes one 1 KiB row
-    per wavefront: two rows would slow small transfers over the host link."""
+def test_host_staging_copies_move_one_row_a_wavefront(record, call, pool):
+    """Few rows or many, a copy to or from host memory takes one 1 KiB row per
+    wavefront: two rows slow small transfers over the link."""
     tile = pool[2] * pool[3] * pool[4] * 2
     for n in (1, 5, 60):
         got = record([dict(call=call, pool_args=pool, blocks=list(range(n)), staging="host")])[0]
@@ -48,10 +48,12 @@ def test_staging_copies_move_one_row_a_wavefront(record, call, pool):
         assert one["grid"] == one["items"] == n * 2 * pool[0] * tile // 1024
 
 
-def test_small_stages_move_two_rows_a_wavefront(record):
-    """Pool to pool, up to one round of resident wavefronts (8192 rows)."""
-    one, two = record([dict(call="stage", pool_args=(1, 64, 16, 32, 128), src=list(range(n)), dst=list(range(n)))
-                       for n in (32, 33)])
+@pytest.mark.parametrize("call", ["stage", "pack", "unpack"])
+def test_small_copies_move_two_rows_a_wavefront(record, call):
+    """On the GPU, up to one round of resident wavefronts (8192 rows)."""
+    where = [dict(src=list(range(n)), dst=list(range(n))) if call == "stage" else
+             dict(blocks=list(range(n)), staging="device") for n in (32, 33)]
+    one, two = record([dict(call=call, pool_args=(1, 64, 16, 32, 128), **w) for w in where])
     assert one["launches"][0]["template"][3] == 2 and one["launches"][0]["grid"] == 32 * 2 * 64
     assert two["launches"][0]["template"][3] == 1 and two["launches"][0]["grid"] == 33 * 2 * 128
 
