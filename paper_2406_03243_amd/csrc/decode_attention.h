@@ -34,7 +34,7 @@ constexpr int kWaitLgkm0 = 0xC07F;
 
 constexpr int kPartTokens = 2048;    // most tokens per partition
 constexpr int kMinPartTokens = 256;  // fewest tokens a sequence is split down to
-constexpr int kWholeTokens = 512;    // a call of no longer sequences splits none
+constexpr int kWholeTokens = 768;    // a call of no longer sequences splits none
 constexpr int kAttnMaxBatch = 256;   // sequences per call (their partitions ride in the kernel arguments)
 // A partial result record: the partition's maximum score m (natural base),
 // its weight sum l, two floats of padding, then the D weighted V sums, so
@@ -83,9 +83,9 @@ struct AttnReduceArgs {
 
 // Tokens per partition of a sequence of n tokens cut into `parts` partitions:
 // equal shares, whole rounds of the four wavefronts' 16-token groups.
-__host__ __device__ inline int32_t attn_part_len(int32_t n, uint32_t parts)
+inline int32_t attn_part_len(int32_t n, uint32_t parts)
 {
-    const int64_t share = (static_cast<int64_t>(n) + parts - 1) / parts;
+    const uint32_t share = (static_cast<uint32_t>(n) + parts - 1) / parts;
     return static_cast<int32_t>((share + 63) / 64 * 64);
 }
 
@@ -755,9 +755,9 @@ inline uint32_t attn_parts(int32_t n, int32_t part)
 {
     if (n <= part)
         return 1u;
-    const uint32_t parts = static_cast<uint32_t>((static_cast<int64_t>(n) + part - 1) / part);
-    const int32_t len = attn_part_len(n, parts);     // rounded up to 64: perhaps fewer are enough
-    return static_cast<uint32_t>((static_cast<int64_t>(n) + len - 1) / len);
+    const uint32_t parts = (static_cast<uint32_t>(n) + part - 1) / part;
+    const uint32_t len = attn_part_len(n, parts);    // rounded up to 64: perhaps fewer are enough
+    return (static_cast<uint32_t>(n) + len - 1) / len;
 }
 
 // Bytes of the partial results of a call (sequences of one partition leave none).
@@ -779,39 +779,61 @@ inline int attn_record_bytes(const int32_t *ctx_lens, int32_t batch, int32_t par
 // Most tokens per partition of a call: kPartTokens, unless that leaves the
 // chip short of workgroups.  A partition costs a workgroup's start and end
 // (block ids, query rows, the first rows' latency, the merge, a record) and a
-// share of the merge kernel, so longer is better as long as every CU has
-// work: shares of about kAttnWorkgroups workgroups, two a CU.  Measured, one
-// layer of 8 KV heads: one sequence of 32000 tokens, partitions of 2048 / 1024
-// / 512 / 256 tokens 42 / 28.6 / 30.1 / 31.9 us; three of up to 3000, 2048 /
-// 512 / 256 / 128 31.4 / 15.8 / 14.2 / 14.1 us; 32 layers of one sequence of 32000, 2048 /
-// 1024 / 512 703 / 729 / 773 us.  The merge is a launch of its own, so short
-// sequences stay whole (one of 300 tokens 10.9 us, in two 14.0; 80 layers of
-// one of 500 33 against 39).  Records of a finer split stay within
-// kSplitBytes, half of LLMIG_DECODE_SCRATCH_BYTES, so that every entry point
-// cuts a call alike.
-constexpr int64_t kAttnWorkgroups = 512;
-constexpr int64_t kSplitBytes = LLMIG_DECODE_SCRATCH_BYTES / 2;
+// share of the merge kernel, so a call is cut no finer than fills the chip,
+// counted in workgroups: one a CU for head_dim 128, two (of half the bytes)
+// for 64.  Past that a cut can only even out the CUs: calls that need the merge
+// anyway are cut to the next whole number a CU, up to three.  Measured, partitions
+// of 2048 / 1536 / 1024 / 768 / 512 / 384 / 256 tokens (workgroups), us:
+//   head_dim 128, 8 heads, three of up to 9280: 34.5 (88), 31.7, 27.4, 25.3
+//     (224), 27.2 (328), 26.1, 27.1; 4 heads, 28 of up to 4170: 37.5 (160),
+//     30.2, 29.0 (256), 31.9, 30.1, 31.9, 32.1
+//   two a CU: five of up to 29082, 71.0 (336), 67.0 (448), 68.3 (664), 68.4
+//   three a CU: 4 layers of 13 heads, seven of up to 6412, 91.3 (624), 84.5
+//     (768); 8 layers of 8, four of up to 6823, 90.0 (576), 85.6 (768); four a
+//     CU: 640 to 990 workgroups, level
+//   head_dim 64, 4 heads, 14 of up to 11364: 29.3 (156), 26.3, 24.2 (268),
+//     22.8, 21.7 (508), 22.7, 22.4; 32 heads, 2 of 23635: 50.6 (480), 55.3
+//     (640), 54.9, 53.9, 51.8
+// The merge is a launch of its own, so a call of short sequences stays whole
+// (two of up to 757 13.8 against 15 cut, 16 of up to 569 12.6 and 15.3, two of
+// up to 933 17.0 and 13.8), and so does one whose longest partition would
+// become less than a tenth shorter.
+constexpr int64_t kAttnCUs = 256, kAttnWorkgroupsMost = 3 * kAttnCUs;
+
+// Workgroups per layer and KV head of a call cut into partitions of at most
+// `part` tokens.
+inline int64_t attn_items(const int32_t *ctx_lens, int32_t batch, int32_t part)
+{
+    int64_t n = 0;
+    for (int32_t b = 0; b < batch; ++b)
+        n += attn_parts(ctx_lens[b], part);
+    return n;
+}
 
 inline int32_t attn_part_tokens(const int32_t *ctx_lens, int32_t batch, int64_t num_layers, int64_t kv_heads,
-                                int64_t q_heads, int64_t head_dim)
+                                int64_t head_dim)
 {
-    int64_t tokens = 0, work = 0;
     int32_t longest = 0;
-    for (int32_t b = 0; b < batch; ++b) {
-        tokens += ctx_lens[b];
+    for (int32_t b = 0; b < batch; ++b)
         longest = std::max(longest, ctx_lens[b]);
-    }
-    if (longest <= kWholeTokens || __builtin_mul_overflow(tokens, num_layers, &work) || __builtin_mul_overflow(work, kv_heads, &work) ||
-        work >= kAttnWorkgroups * kPartTokens)
+    int64_t per_item = 0, whole = 0;
+    if (longest <= kWholeTokens || __builtin_mul_overflow(num_layers, kv_heads, &per_item) ||
+        __builtin_mul_overflow(per_item, attn_items(ctx_lens, batch, kPartTokens), &whole))
         return kPartTokens;
-    int32_t part = static_cast<int32_t>((work / kAttnWorkgroups + 63) / 64 * 64);
-    part = std::max(std::min(part, kPartTokens), kMinPartTokens);
-    int64_t bytes = 0;
-    while (part < kPartTokens &&
-           (attn_record_bytes(ctx_lens, batch, part, num_layers, q_heads, head_dim, &bytes) != LLMIG_OK ||
-            bytes > kSplitBytes))
-        part = std::min(2 * part, kPartTokens);
-    return part;
+    int64_t most = head_dim == 64 ? 2 * kAttnCUs : kAttnCUs;
+    while (whole > most && most < kAttnWorkgroupsMost && longest > kPartTokens)
+        most += kAttnCUs;
+    if (whole > most)
+        return kPartTokens;
+    int32_t lo = kMinPartTokens / 64, hi = kPartTokens / 64;    // the shortest that keeps to `most`
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) / 2;
+        if (attn_items(ctx_lens, batch, 64 * mid) * per_item <= most)
+            hi = mid;
+        else
+            lo = mid + 1;
+    }
+    return 10 * 64 * lo > 9 * std::min(longest, kPartTokens) ? kPartTokens : 64 * lo;
 }
 
 // Calls of long partitions leave some of the chip's workgroup slots empty, by

@@ -1163,7 +1163,7 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
         a.dst_layer_bytes = static_cast<uint32_t>(static_cast<uint64_t>(mig.dst->num_blocks) * mig.dst->tile_bytes);
         a.dst_blocks = mig.dst->num_blocks;
     }
-    int32_t part = attn_part_tokens(ctx_lens, batch, pool->num_layers, pool->num_kv_heads, q_heads, pool->head_dim);
+    int32_t part = attn_part_tokens(ctx_lens, batch, pool->num_layers, pool->num_kv_heads, pool->head_dim);
     int64_t need = 0;
     if (attn_record_bytes(ctx_lens, batch, part, pool->num_layers, q_heads, pool->head_dim, &need) != LLMIG_OK ||
         need > ws_bytes)
@@ -1265,7 +1265,7 @@ int llmig_decode_attention_workspace(const int32_t *ctx_lens, int32_t batch, int
     // what the split for any number of KV heads takes
     for (int32_t group = 1; rc == LLMIG_OK && group <= 16 && q_heads % group == 0; group *= 2) {
         int64_t v = 0;
-        const int32_t part = attn_part_tokens(ctx_lens, batch, num_layers, q_heads / group, q_heads, head_dim);
+        const int32_t part = attn_part_tokens(ctx_lens, batch, num_layers, q_heads / group, head_dim);
         rc = attn_record_bytes(ctx_lens, batch, part, num_layers, q_heads, head_dim, &v);
         need = std::max(need, v);
     }

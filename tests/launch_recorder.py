@@ -37,7 +37,22 @@ class ConvertArgs(ctypes.Structure):
                 ("ids", U32 * (2 * INLINE))]
 
 
-STRUCTS = {"copy_rows": CopyArgs, "copy_tiles": CopyArgs, "convert_slabs": ConvertArgs, "convert_tiles": ConvertArgs}
+class AttnArgs(ctypes.Structure):
+    _fields_ = [("k_tab", P), ("q", P), ("tables", P), ("ws", P), ("out", P), ("scale", ctypes.c_float),
+                ("num_layers", U32), ("batch", U32), ("q_heads", U32), ("kv_heads", U32), ("block_size", U32),
+                ("table_stride", U32), ("item_base", U32), ("n_records", U32), ("part_tokens", U32),
+                ("item_end", U32 * MAX_BATCH), ("ctx", I32 * MAX_BATCH), ("seq", U32 * (MAX_BATCH // 2)),
+                ("dst_tab", P), ("mig_ids", P), ("mig_seq", I32), ("mig_from", I32), ("mig_to", I32),
+                ("dst_layer_bytes", U32), ("dst_blocks", I32)]
+
+
+class AttnReduceArgs(ctypes.Structure):
+    _fields_ = [("ws", P), ("out", P), ("num_layers", U32), ("batch", U32), ("q_heads", U32), ("head_dim", U32),
+                ("n_records", U32), ("row_base", U64), ("seqs", U32), ("seq_end", U32 * MAX_BATCH),
+                ("seq", ctypes.c_uint8 * MAX_BATCH)]
+
+
+STRUCTS = {"attn_partial_mfma": AttnArgs, "attn_reduce": AttnReduceArgs, "copy_rows": CopyArgs, "copy_tiles": CopyArgs, "convert_slabs": ConvertArgs, "convert_tiles": ConvertArgs}
 
 
 class Desc(ctypes.Structure):
@@ -113,12 +128,31 @@ def fuse(call, pool_args, blocks, staging, layouts=(0, 0), staging_layouts=(0, 0
     return getattr(lib, "llmig_" + call)(p, pa, n, 0, where, size, None)
 
 
+def decode(pool_args, ctx, group, workspace="full"):
+    """workspace: "full" (the size the library returns), "least" (2048 tokens a
+    partition), "none" (llmig_decode_attention_noalloc)."""
+    layers, _, bs, heads, dim = pool_args
+    c, pc, _ = ids(ctx)
+    q_heads, stride = heads * group, max(1, max(-(-n // bs) for n in ctx))
+    size = ctypes.c_int64()
+    assert lib.llmig_decode_attention_workspace(pc, len(ctx), layers, q_heads, dim, ctypes.byref(size)) == 0
+    least = layers * q_heads * (dim + 4) * 4 * sum(-(-n // 2048) for n in ctx)
+    assert size.value >= least
+    q, tables, out, ws = (ctypes.c_void_p(a << 44) for a in (1, 2, 3, 4))
+    scale = ctypes.c_float(0.1)
+    if workspace == "none":
+        return lib.llmig_decode_attention_noalloc(pool(*pool_args), 0, q, len(ctx), q_heads, tables, stride, pc,
+                                                  scale, out, None)
+    return lib.llmig_decode_attention(pool(*pool_args), 0, q, len(ctx), q_heads, tables, stride, pc, scale, ws,
+                                      ctypes.c_int64(size.value if workspace == "full" else least), out, None)
+
+
 def main():
     out = []
     for c in json.load(sys.stdin):
         launches.clear()
         kind = c.pop("call")
-        rc = stage(**c) if kind == "stage" else fuse(kind, **c)
+        rc = {"stage": stage, "decode": decode}[kind](**c) if kind in ("stage", "decode") else fuse(kind, **c)
         out.append({"rc": rc, "launches": list(launches)})
     json.dump(out, sys.stdout)
 

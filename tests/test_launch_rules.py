@@ -111,3 +111,135 @@ def test_pairs_are_ordered_only_where_it_pays(record, call):
             assert in_order([d for _, d in pairs], max(dst)), (pool, n)
         else:
             assert pairs == list(zip(src, dst)), (pool, n)
+
+
+# ---- decode attention ---------------------------------------------------------
+
+def partitions(launches):
+    """{sequence: [(first token, end)]} of a call as its kernels will number
+    them, and its workgroups, checked: sequences of several partitions come
+    first, longest partition first, launches cover every item once, and the
+    merge reads the records the partial kernel leaves."""
+    partial = [x for x in launches if x["kernel"] == "attn_partial_mfma"]
+    a = partial[0]
+    per_item = a["kv_heads"] * a["num_layers"]
+    out, first, lengths = {}, 0, []
+    for s in range(a["batch"]):
+        end, n = a["item_end"][s], a["ctx"][s]
+        word = a["seq"][s // 2] >> (16 * (s % 2))
+        b, plen = word & 0xff, (word >> 8 & 0xff) * 64
+        parts = end - first
+        assert b not in out and parts >= 1
+        if parts == 1:
+            out[b] = [(0, n)]
+        else:
+            out[b] = [(i * plen, min(n, (i + 1) * plen)) for i in range(parts)]
+            assert out[b][-1][0] < n <= parts * plen
+        lengths.append((parts == 1, -(plen if parts > 1 else n)))
+        assert max(e - t for t, e in out[b]) <= a["part_tokens"] <= 2048
+        first = end
+    assert lengths == sorted(lengths)
+    assert a["n_records"] == sum(len(p) for p in out.values() if len(p) > 1)
+    items, at = first, 0
+    for x in partial:
+        assert x["item_base"] == at and x["grid"] % per_item == 0 and x["grid"] // per_item >= 1
+        assert x["grid"] <= 1 << 22 or x["grid"] == per_item
+        at += x["grid"] // per_item
+    assert at == items
+    merge = [x for x in launches if x["kernel"] == "attn_reduce"]
+    several = [b for b in out if len(out[b]) > 1]
+    assert bool(merge) == bool(several)
+    if merge:
+        m = merge[0]
+        assert m["seqs"] == len(several) and m["seq"][:len(several)] == several
+        assert np.diff([0] + m["seq_end"][:len(several)]).tolist() == [len(out[b]) for b in several]
+        rows, per_wg = m["num_layers"] * m["seqs"] * m["q_heads"], 256 // (m["head_dim"] // 4) if m["template"][1] == 1 else 1
+        assert m["template"][1] > 1 or max(len(p) for p in out.values()) <= 8
+        at = 0
+        for x in merge:
+            assert x["row_base"] == at and x["grid"] <= 1 << 22
+            at += x["grid"] * per_wg
+        assert rows <= at < rows + per_wg
+    return out, items * per_item
+
+
+def decode(pool, ctx, group=1, workspace="full"):
+    return dict(call="decode", pool_args=pool, ctx=ctx, group=group, workspace=workspace)
+
+
+def test_attention_partitions_cover_every_token(record):
+    """Random calls, batches up to 256, empty sequences among them."""
+    g = np.random.default_rng(7)
+    calls = []
+    for k in range(60):
+        batch = int(g.choice([1, 3, 17, 64, 255, 256]))
+        pool = (int(g.integers(1, 5)), 8, int(g.choice([1, 12, 16, 32])), int(g.choice([1, 4, 8])), int(g.choice([64, 128])))
+        ctx = np.exp(g.uniform(0, np.log(int(g.choice([500, 3000, 40000]))), batch)).astype(int)
+        ctx[g.random(batch) < 0.1] = 0
+        calls.append(decode(pool, ctx.tolist(), int(g.choice([1, 4, 16])), ["full", "least"][k % 2]))
+    for c, got in zip(calls, record(calls)):
+        assert got["rc"] == 0, c
+        parts, _ = partitions(got["launches"])
+        for b, n in enumerate(c["ctx"]):
+            assert parts[b][0][0] == 0 and parts[b][-1][1] == n
+            assert all(x[1] == y[0] and y[0] % 64 == 0 for x, y in zip(parts[b], parts[b][1:]))
+
+
+def test_attention_runs_as_several_launches(record):
+    """A launch holds 2^22 workgroups: 256 items of 128 layers of 128 heads, and
+    as many rows of the merge (16 a workgroup for head_dim 64)."""
+    got, wide = record([decode((128, 8, 16, 128, 64), [5000] * 256), decode((160, 8, 16, 128, 64), [5000] * 256, 16)])
+    _, workgroups = partitions(got["launches"])
+    assert workgroups == 256 * 3 * 128 * 128 and [x["kernel"] for x in got["launches"]] == ["attn_partial_mfma"] * 3 + ["attn_reduce"]
+    partitions(wide["launches"])
+    assert sum(x["kernel"] == "attn_reduce" for x in wide["launches"]) == 2
+
+
+# one layer of 8 heads unless said: calls that fill the chip in whole partitions
+# of 2048, or whose sequences are short, are cut no further
+UNCUT = [((1, 8, 16, 8, 128), [1000, 200] * 32), ((1, 8, 16, 8, 64), [1000, 200] * 32),
+         ((1, 8, 16, 8, 128), [768]), ((8, 8, 16, 8, 128), [1364] * 4), ((4, 8, 16, 8, 64), [1439] * 17),
+         ((1, 8, 16, 32, 64), [13646] * 4), ((1, 8, 16, 32, 128), [22639] * 3),
+         ((32, 8, 16, 8, 128), [962, 500, 400])]
+
+
+@pytest.mark.parametrize("workspace", ["full", "none"])
+def test_attention_is_not_cut_past_a_full_chip(record, workspace):
+    for (pool, ctx), got in zip(UNCUT, record([decode(p, c, 1, workspace) for p, c in UNCUT])):
+        parts, _ = partitions(got["launches"])
+        assert all(len(parts[b]) == max(1, -(-n // 2048)) for b, n in enumerate(ctx)), (pool, ctx)
+
+
+def test_attention_cuts_fill_the_chip_and_no_more(record):
+    """Short of workgroups, a call is cut to at most one a CU (head_dim 128) or
+    two (64), where the merge is needed anyway to the next whole number up to
+    three, and to no fewer than half of that unless partitions reach 256
+    tokens."""
+    g = np.random.default_rng(11)
+    calls = []
+    for _ in range(80):
+        pool = (int(g.choice([1, 1, 2, 4])), 8, 16, int(g.choice([1, 2, 4, 8])), int(g.choice([64, 128])))
+        calls.append(decode(pool, np.exp(g.uniform(np.log(769), np.log(30000), int(g.integers(1, 9)))).astype(int).tolist(), 4))
+    cut = 0
+    for c, got in zip(calls, record(calls)):
+        (layers, _, _, heads, dim), ctx = c["pool_args"], c["ctx"]
+        parts, workgroups = partitions(got["launches"])
+        whole = layers * heads * sum(-(-n // 2048) for n in ctx)
+        if all(len(parts[b]) <= -(-n // 2048) for b, n in enumerate(ctx)):
+            continue
+        cut += 1
+        most = 512 if dim == 64 else 256
+        if max(ctx) > 2048:
+            most = max(most, min(768, -(-whole // 256) * 256))
+        assert whole <= most and workgroups <= most, c
+        longest = max(e - t for p in parts.values() for t, e in p)
+        assert longest == 256 or workgroups >= most // 2, (c, workgroups, longest)
+        assert longest <= 0.9 * min(2048, max(ctx)) + 63
+    assert cut > 30
+
+
+def test_attention_of_the_smaller_workspace_has_partitions_of_2048(record):
+    pool, ctx = (1, 8, 16, 8, 128), [3000, 900, 700, 0]
+    full, least = record([decode(pool, ctx, 4, w) for w in ("full", "least")])
+    assert len(partitions(full["launches"])[0][0]) > 2
+    assert [len(partitions(least["launches"])[0][b]) for b in range(4)] == [2, 1, 1, 1]
