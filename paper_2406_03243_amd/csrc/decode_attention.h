@@ -781,7 +781,8 @@ inline int attn_record_bytes(const int32_t *ctx_lens, int32_t batch, int32_t par
 // (block ids, query rows, the first rows' latency, the merge, a record) and a
 // share of the merge kernel, so a call is cut no finer than fills the chip,
 // counted in workgroups: one a CU for head_dim 128, two (of half the bytes)
-// for 64.  Past that a cut can only even out the CUs: calls that need the merge
+// for 64 and for calls of no sequence over 2048 tokens, whose workgroups are
+// short.  Past that a cut can only even out the CUs: calls that need the merge
 // anyway are cut to the next whole number a CU, up to three.  Measured, partitions
 // of 2048 / 1536 / 1024 / 768 / 512 / 384 / 256 tokens (workgroups), us:
 //   head_dim 128, 8 heads, three of up to 9280: 34.5 (88), 31.7, 27.4, 25.3
@@ -797,7 +798,10 @@ inline int attn_record_bytes(const int32_t *ctx_lens, int32_t batch, int32_t par
 // The merge is a launch of its own, so a call of short sequences stays whole
 // (two of up to 757 13.8 against 15 cut, 16 of up to 569 12.6 and 15.3, two of
 // up to 933 17.0 and 13.8), and so does one whose longest partition would
-// become less than a tenth shorter.
+// become less than a quarter shorter (a tenth, where the merge is needed
+// anyway).  head_dim 128, one layer, whole / 256 / 512 workgroups: 8 heads, 30
+// of up to 2003 41.1 / 35.5 / 28.3, 58 of 4 heads up to 1422 30.4 / 28.2 / 23.9,
+// 59 of 8 heads up to 1202 (472) level.
 constexpr int64_t kAttnCUs = 256, kAttnWorkgroupsMost = 3 * kAttnCUs;
 
 // Workgroups per layer and KV head of a call cut into partitions of at most
@@ -820,8 +824,9 @@ inline int32_t attn_part_tokens(const int32_t *ctx_lens, int32_t batch, int64_t 
     if (longest <= kWholeTokens || __builtin_mul_overflow(num_layers, kv_heads, &per_item) ||
         __builtin_mul_overflow(per_item, attn_items(ctx_lens, batch, kPartTokens), &whole))
         return kPartTokens;
-    int64_t most = head_dim == 64 ? 2 * kAttnCUs : kAttnCUs;
-    while (whole > most && most < kAttnWorkgroupsMost && longest > kPartTokens)
+    const bool merges = longest > kPartTokens;
+    int64_t most = head_dim == 64 || !merges ? 2 * kAttnCUs : kAttnCUs;
+    while (whole > most && most < kAttnWorkgroupsMost && merges)
         most += kAttnCUs;
     if (whole > most)
         return kPartTokens;
@@ -833,19 +838,37 @@ inline int32_t attn_part_tokens(const int32_t *ctx_lens, int32_t batch, int64_t 
         else
             lo = mid + 1;
     }
-    return 10 * 64 * lo > 9 * std::min(longest, kPartTokens) ? kPartTokens : 64 * lo;
+    return 100 * 64 * lo > (merges ? 90 : 75) * std::min(longest, kPartTokens) ? kPartTokens : 64 * lo;
 }
 
-// Calls of long partitions leave some of the chip's workgroup slots empty, by
-// asking for LDS they don't use: with every slot taken more rows are in flight
+// Workgroups a CU that calls of long partitions keep to, by asking for LDS they
+// don't use (0: as many as fit): with every slot taken more rows are in flight
 // than the memory system needs, and each workgroup's own waits (its start, its
-// end) last as long as that queue.  kLongPartLds leaves three workgroups a CU
-// for head_dim 128, four (of up to eight) for 64.  32 layers, head_dim 64, 32
-// heads, mean partition 860 / 1350 / 2048 tokens 137.9 -> 132.7, 170 -> 161,
-// 233 -> 223 us (600 tokens: level, 140: 99 -> 111); head_dim 128, 2000 tokens
-// 658 -> 651, 479 -> 472 (860 tokens: 270 -> 272).
-constexpr int64_t kLongPartTokens64 = 800, kLongPartTokens128 = 1500;
-constexpr size_t kLongPartLds = 15000;
+// end) last as long as that queue.  Three for head_dim 128, four (of up to
+// eight) for 64.  32 layers, head_dim 64, 32 heads, mean partition 860 / 1350 /
+// 2048 tokens 137.9 -> 132.7, 170 -> 161, 233 -> 223 us (600 tokens: level, 140:
+// 99 -> 111); head_dim 128, 2000 tokens 658 -> 651, 479 -> 472 (860 tokens: 270 ->
+// 272).  Where that leaves a second round of a few workgroups it loses: 8
+// layers of 13 heads of 64, two of up to 17421 (1144 workgroups) 98 -> 106,
+// 1248 87 -> 92, 1408 110 -> 117; 1504 gain 7%.  Calls just short of 1024
+// workgroups run as two rounds of two a CU: one layer of 4 heads of 64, 38 of
+// up to 25627 (944) 90 -> 84.5, 8 heads, 28 of up to 14959 (904) 88 -> 75;
+// head_dim 128, 64 of up to 6197 (936) 147 -> 136; 800 workgroups lose 6%.  (The
+// carrying kernel has not been measured so.)
+inline int attn_workgroups_per_cu(int64_t head_dim, int64_t workgroups, int64_t mean_tokens, bool migrating)
+{
+    const int64_t full = head_dim == 64 ? 4 : 3;
+    if (!migrating && workgroups >= 840 && workgroups <= 4 * kAttnCUs && mean_tokens >= 1200)
+        return 2;
+    return 5 * workgroups >= 7 * full * kAttnCUs && mean_tokens >= (head_dim == 64 ? 800 : 1500) ? full : 0;
+}
+
+// Dynamic LDS that keeps n workgroups of the partial kernel a CU (160 KiB of
+// LDS; 17.5 KiB a workgroup for head_dim 64, 33.5 for 128).
+inline size_t attn_spare_lds(int64_t head_dim, int n)
+{
+    return n == 0 ? 0 : n == 2 ? (head_dim == 64 ? 40000 : 24000) : 15000;
+}
 
 // The merge kernel for at most `most` partitions a sequence; returns its rows
 // per workgroup.

@@ -1208,21 +1208,22 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
             a.n_records = items;
         }
     }
-    size_t lds_ids = pool->block_size % 8 == 0
-                         ? 0
-                         : attn_blk_slots(a.part_tokens, a.block_size) * sizeof(int32_t) * (mig.dst ? 2 : 1);
+    size_t lds = pool->block_size % 8 == 0
+                     ? 0
+                     : attn_blk_slots(a.part_tokens, a.block_size) * sizeof(int32_t) * (mig.dst ? 2 : 1);
     int64_t tokens = 0;
     for (int32_t b = 0; b < batch; ++b)
         tokens += ctx_lens[b];
-    if (tokens >= static_cast<int64_t>(items) * (pool->head_dim == 64 ? kLongPartTokens64 : kLongPartTokens128))
-        lds_ids = std::max<size_t>(lds_ids, kLongPartLds);
     const uint64_t per_item = static_cast<uint64_t>(a.kv_heads) * a.num_layers;
+    const int per_cu = attn_workgroups_per_cu(pool->head_dim, static_cast<int64_t>(items * per_item), tokens / items,
+                                              mig.dst != nullptr);
+    lds = std::max(lds, attn_spare_lds(pool->head_dim, per_cu));
     const uint32_t step = static_cast<uint32_t>(std::max<uint64_t>(kMaxGridWorkgroups / per_item, 1u));
     for (uint32_t at = 0; at < items; at += std::min(step, items - at)) {
         a.item_base = at;
         void *args[] = {&a};
         hipError_t e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(std::min(step, items - at) * per_item)),
-                                       dim3(kThreads), args, lds_ids, st);
+                                       dim3(kThreads), args, lds, st);
         if (e != hipSuccess)
             return hip_error(e);
     }

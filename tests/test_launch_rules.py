@@ -198,7 +198,7 @@ def test_attention_runs_as_several_launches(record):
 # one layer of 8 heads unless said: calls that fill the chip in whole partitions
 # of 2048, or whose sequences are short, are cut no further
 UNCUT = [((1, 8, 16, 8, 128), [1000, 200] * 32), ((1, 8, 16, 8, 64), [1000, 200] * 32),
-         ((1, 8, 16, 8, 128), [768]), ((8, 8, 16, 8, 128), [1364] * 4), ((4, 8, 16, 8, 64), [1439] * 17),
+         ((1, 8, 16, 8, 128), [768]), ((8, 8, 16, 8, 128), [1364] * 9), ((4, 8, 16, 8, 64), [1439] * 17),
          ((1, 8, 16, 32, 64), [13646] * 4), ((1, 8, 16, 32, 128), [22639] * 3),
          ((32, 8, 16, 8, 128), [962, 500, 400])]
 
@@ -211,10 +211,10 @@ def test_attention_is_not_cut_past_a_full_chip(record, workspace):
 
 
 def test_attention_cuts_fill_the_chip_and_no_more(record):
-    """Short of workgroups, a call is cut to at most one a CU (head_dim 128) or
-    two (64), where the merge is needed anyway to the next whole number up to
-    three, and to no fewer than half of that unless partitions reach 256
-    tokens."""
+    """Short of workgroups, a call is cut to at most two a CU (one for sequences
+    over 2048 tokens of head_dim 128), where the merge is needed anyway to the
+    next whole number up to three, and to no fewer than half of that unless
+    partitions reach 256 tokens."""
     g = np.random.default_rng(11)
     calls = []
     for _ in range(80):
@@ -228,13 +228,13 @@ def test_attention_cuts_fill_the_chip_and_no_more(record):
         if all(len(parts[b]) <= -(-n // 2048) for b, n in enumerate(ctx)):
             continue
         cut += 1
-        most = 512 if dim == 64 else 256
+        most = 512 if dim == 64 or max(ctx) <= 2048 else 256
         if max(ctx) > 2048:
             most = max(most, min(768, -(-whole // 256) * 256))
         assert whole <= most and workgroups <= most, c
         longest = max(e - t for p in parts.values() for t, e in p)
         assert longest == 256 or workgroups >= most // 2, (c, workgroups, longest)
-        assert longest <= 0.9 * min(2048, max(ctx)) + 63
+        assert longest <= (0.9 if max(ctx) > 2048 else 0.75) * min(2048, max(ctx)) + 63
     assert cut > 30
 
 
@@ -243,3 +243,24 @@ def test_attention_of_the_smaller_workspace_has_partitions_of_2048(record):
     full, least = record([decode(pool, ctx, 4, w) for w in ("full", "least")])
     assert len(partitions(full["launches"])[0][0]) > 2
     assert [len(partitions(least["launches"])[0][b]) for b in range(4)] == [2, 1, 1, 1]
+
+
+# pool, lengths, workgroups a CU that the launch leaves room for (0: no limit)
+ROOM = [((8, 8, 16, 13, 64), [17400] * 1 + [4000], 0),          # 1144: a second round of a few would lose
+        ((32, 8, 16, 13, 64), [8000], 4), ((32, 8, 16, 13, 128), [8000], 3),
+        ((1, 8, 16, 13, 128), [16000] * 10, 0), ((4, 8, 16, 8, 128), [16000] * 5, 3),
+        ((1, 8, 16, 8, 64), [14000] * 16, 2), ((1, 8, 16, 8, 128), [14000] * 16, 2),
+        ((1, 8, 16, 8, 64), [12000] * 16, 0),                   # 768
+        ((1, 8, 12, 8, 64), [14000] * 16, 2),                   # block ids in LDS beside it
+        ((32, 8, 16, 32, 64), [700] * 8, 0), ((32, 8, 16, 32, 128), [1400] * 8, 0)]
+
+
+def test_attention_of_long_partitions_leaves_room(record):
+    static = {64: 17920, 128: 34304}
+    for (pool, ctx, want), got in zip(ROOM, record([decode(p, c) for p, c, _ in ROOM])):
+        parts, workgroups = partitions(got["launches"])
+        lds = got["launches"][0]["lds"]
+        if want == 0:
+            assert lds == 0, (pool, ctx, workgroups)
+        else:
+            assert 163840 // (static[pool[4]] + lds) == want, (pool, ctx, workgroups, lds)
