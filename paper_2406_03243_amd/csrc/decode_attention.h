@@ -54,6 +54,8 @@ struct AttnArgs {
     float scale;
     uint32_t num_layers, batch, q_heads, kv_heads, block_size, table_stride;
     uint32_t item_base;         // this launch's first item
+    uint32_t layer_items;       // 0: item by item, all layers of one in a row; else layer by
+                                // layer, and this many items in this launch
     uint32_t n_records;         // items that leave a partial result
     uint32_t part_tokens;       // most tokens of a partition in this call
     uint32_t item_end[kAttnMaxBatch];  // items of the first s + 1 sequences
@@ -375,12 +377,13 @@ attn_partial_mfma(const AttnArgs a)
     // on one XCD: linear workgroup w is the (w / 8)-th on XCD w % 8.  The
     // tail of the grid that does not fill whole rounds of 8 * kv_heads keeps
     // the plain order.  Items run longest first, all layers of one after the
-    // other, so the last workgroups to run are short ones.
+    // other, so the last workgroups to run are short ones (see
+    // attn_layer_by_layer for the calls that don't).
     uint32_t item, g, layer;
     {
         const uint32_t H = a.kv_heads, lin = blockIdx.x;
         const uint32_t full = gridDim.x - gridDim.x % (8u * H);
-        uint32_t unit;                    // (item, layer) in row-major order
+        uint32_t unit;                    // (item, layer) in the launch's order
         if (lin < full) {
             const uint32_t k = lin / 8u;
             g = k % H;
@@ -389,8 +392,13 @@ attn_partial_mfma(const AttnArgs a)
             g = lin % H;
             unit = lin / H;
         }
-        item = unit / a.num_layers;
-        layer = unit - item * a.num_layers;
+        if (a.layer_items) {
+            layer = unit / a.layer_items;
+            item = unit - layer * a.layer_items;
+        } else {
+            item = unit / a.num_layers;
+            layer = unit - item * a.num_layers;
+        }
         item = uniform(item + a.item_base);
         layer = uniform(layer);
     }
@@ -861,6 +869,19 @@ inline int attn_workgroups_per_cu(int64_t head_dim, int64_t workgroups, int64_t 
     if (!migrating && workgroups >= 840 && workgroups <= 4 * kAttnCUs && mean_tokens >= 1200)
         return 2;
     return 5 * workgroups >= 7 * full * kAttnCUs && mean_tokens >= (head_dim == 64 ? 800 : 1500) ? full : 0;
+}
+
+// Whether a call runs layer by layer instead of longest item first: batches of
+// many short sequences of head_dim 64, whose neighbours then read and write one
+// layer's tensors (what exactly that saves was not traced).  Longest first ->
+// layer by layer: 73 layers of 32 heads, 5 of up to 208 tokens 66.4 -> 62.0 us,
+// 80 of 4, 60 of up to 394 145 -> 137, 32 of 13, 37 of up to 391 110 -> 103.
+// Elsewhere the end of the launch decides: 73 layers of 4 heads of 64, 32 of up
+// to 633 (mean 280) 14% slower, 80 of 8 heads of 128, 12 of up to 122 (7680
+// workgroups) 51 -> 55, decode steps of long sequences up to 48% slower.
+inline bool attn_layer_by_layer(int64_t head_dim, int64_t workgroups, int64_t mean_tokens)
+{
+    return head_dim == 64 && workgroups >= 8192 && mean_tokens < 200;
 }
 
 // Dynamic LDS that keeps n workgroups of the partial kernel a CU (160 KiB of

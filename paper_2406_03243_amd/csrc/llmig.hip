@@ -1215,15 +1215,17 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
     for (int32_t b = 0; b < batch; ++b)
         tokens += ctx_lens[b];
     const uint64_t per_item = static_cast<uint64_t>(a.kv_heads) * a.num_layers;
-    const int per_cu = attn_workgroups_per_cu(pool->head_dim, static_cast<int64_t>(items * per_item), tokens / items,
-                                              mig.dst != nullptr);
+    const int64_t workgroups = static_cast<int64_t>(items * per_item);
+    const int per_cu = attn_workgroups_per_cu(pool->head_dim, workgroups, tokens / items, mig.dst != nullptr);
+    const bool by_layer = attn_layer_by_layer(pool->head_dim, workgroups, tokens / items);
     lds = std::max(lds, attn_spare_lds(pool->head_dim, per_cu));
     const uint32_t step = static_cast<uint32_t>(std::max<uint64_t>(kMaxGridWorkgroups / per_item, 1u));
     for (uint32_t at = 0; at < items; at += std::min(step, items - at)) {
+        const uint32_t here = std::min(step, items - at);
         a.item_base = at;
+        a.layer_items = by_layer ? here : 0u;
         void *args[] = {&a};
-        hipError_t e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(std::min(step, items - at) * per_item)),
-                                       dim3(kThreads), args, lds, st);
+        hipError_t e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(here * per_item)), dim3(kThreads), args, lds, st);
         if (e != hipSuccess)
             return hip_error(e);
     }

@@ -20,13 +20,17 @@ with n = ctx[b] tokens, u = 2^-24 (fp32 unit roundoff) and lambda = 8:
   eps_p the kernel feeds each weight to the P.V product as its 16-bit
           rounding plus the 16-bit rounding of the remainder: relative
           error 2^-16 for bf16 (8-bit significands), 2^-22 for fp16.
-  depth the longest chain of fp32 additions behind one output: the 16
-          terms of one matrix-core product, then a wavefront's token groups
-          of its partition (two products each, the weight's high and low
-          parts; a wavefront takes every fourth group of 16 tokens of a
-          partition of 2048), the merge of four wavefronts and the merge of
-          ceil(n / 2048) partitions:
-              depth(n) = 16 + 2 * ceil(min(n, 2048) / 64) + 4 + ceil(n / 2048).
+  depth the longest chain of fp32 additions behind one output: the 32
+          terms of one matrix-core product (16 tokens, the weight's high and
+          low parts), then a wavefront's token groups of its partition (a
+          wavefront takes every fourth group of 16 tokens), the merge of
+          four wavefronts and the merge of the sequence's partitions (each
+          of SUB groups of lanes takes every SUB-th, then they meet; SUB is
+          1 up to eight partitions, else 1024 / D):
+              depth = 32 + ceil(p / 64) + 4 + (k if k <= 8 else ceil(k / SUB) + SUB)
+          for a sequence of k partitions of at most p tokens, as the library
+          cuts the call (``partitions`` below, held to what the library
+          launches by tests/test_launch_rules.py).
           In the probabilistic rounding-error model (Higham and Mary, 2019)
           a chain of k additions is off by lambda * sqrt(k) * u of the sum
           of the magnitudes of its terms with probability at least
@@ -48,9 +52,8 @@ with n = ctx[b] tokens, u = 2^-24 (fp32 unit roundoff) and lambda = 8:
   u     absolute floor, for rows whose A is 0 (a sequence of no tokens,
           whose output the kernel sets to exactly 0).
 
-Dropping one 2048-token partition of a 50,000-token sequence moves the
-output by ~2e-3; this bound is ~1e-4 there, and tests/test_attn_tolerance.py
-checks on the CPU that every such drop is rejected.
+tests/test_attn_tolerance.py checks on the CPU that losing one partition of
+any case, as the library cuts it, is rejected.
 """
 from __future__ import annotations
 
@@ -66,11 +69,50 @@ LAMBDA = 8.0
 U32 = 2.0 ** -24
 EPS_P = {"bf16": 2.0 ** -16, "fp16": 2.0 ** -22}
 
-# The library splits a call into (sequence, partition) items of 2048 tokens
-# and launches the partial kernel on 128 items at a time; the tests use the
-# split to drop exactly what one item, or one launch, covers.
-PART_TOKENS = 2048
-ITEMS_PER_LAUNCH = 128
+# How the library cuts a call: whole sequences up to PART_TOKENS tokens, finer
+# where that leaves the chip short of workgroups.
+PART_TOKENS, MIN_PART_TOKENS, WHOLE_TOKENS, CUS = 2048, 256, 768, 256
+
+
+def _parts(n: int, part: int):
+    """Number and length of the partitions of an n-token sequence."""
+    if n <= part:
+        return 1, n
+    k = -(-n // part)
+    length = -(-(-(-n // k)) // 64) * 64
+    return -(-n // length), length
+
+
+def part_tokens(ctx, num_layers: int, kv_heads: int, head_dim: int) -> int:
+    """Most tokens of a partition of a call with a workspace of the size the
+    library asks for."""
+    longest, per_item = max(ctx), num_layers * kv_heads
+    workgroups = lambda part: per_item * sum(_parts(n, part)[0] for n in ctx)
+    whole = workgroups(PART_TOKENS)
+    merges = longest > PART_TOKENS
+    most = 2 * CUS if head_dim == 64 or not merges else CUS
+    while merges and whole > most and most < 3 * CUS:
+        most += CUS
+    if longest <= WHOLE_TOKENS or whole > most:
+        return PART_TOKENS
+    part = next(p for p in range(MIN_PART_TOKENS, PART_TOKENS + 1, 64) if workgroups(p) <= most)
+    return PART_TOKENS if 100 * part > (90 if merges else 75) * min(longest, PART_TOKENS) else part
+
+
+def partitions(ctx, num_layers: int, kv_heads: int, head_dim: int, workspace: str = "full"):
+    """The (first token, end) ranges of every sequence of a call; workspace
+    "least": one of the smallest size the library takes (a record for each
+    PART_TOKENS tokens begun), which may not hold the records of a finer cut."""
+    part = part_tokens(ctx, num_layers, kv_heads, head_dim)
+    records = sum(k for k, _ in (_parts(n, part) for n in ctx) if k > 1)
+    if workspace == "least" and records > sum(-(-n // PART_TOKENS) for n in ctx):
+        part = PART_TOKENS
+    out = []
+    for n in ctx:
+        k, length = _parts(n, part)
+        out.append([(0, n)] if k == 1 else [(t, min(n, t + length)) for t in range(0, n, length)])
+    return out
+
 
 # layers, blocks, block_size, kv_heads, head_dim, group, context lengths, dtype, V positive
 CASES = [
@@ -78,9 +120,8 @@ CASES = [
     (2, 200, 16, 4, 64, 1, [513, 31, 7], "bf16", False),
     (1, 400, 16, 2, 128, 4, [4096, 5, 2000], "bf16", False),
     (3, 100, 8, 1, 64, 2, [96, 95, 97, 1], "fp16", False),
-    (1, 3200, 16, 1, 128, 2, [50000, 49999, 40000], "fp16", False),  # 70 partitions of 2048
-    (1, 8400, 16, 1, 128, 2, [131072, 120000, 20000], "fp16", False), # 133 items: two launches,
-                                                                      # the third sequence spans both
+    (1, 3200, 16, 1, 128, 2, [50000, 49999, 40000], "fp16", False),  # ~245 partitions of 576
+    (1, 8400, 16, 1, 128, 2, [131072, 120000, 20000], "fp16", False), # partitions of over 1000 tokens
     (2, 120, 16, 1, 128, 16, [700, 33], "bf16", False),               # 16 query heads on one KV head
     (1, 300, 4, 2, 64, 4, [1000, 3, 62], "bf16", False),              # 4-token blocks
     (1, 3200, 16, 1, 128, 2, [50000, 49999, 40000], "bf16", True),    # V in [0, 1]: output far from 0
@@ -88,8 +129,24 @@ CASES = [
 ]
 
 
+_LONG = [4100 + 20 * i for i in range(30)]
+_MIXED = _LONG + [2000 - 17 * i for i in range(25)]
+# Calls large enough to keep partitions of up to 2048 tokens, and the launch
+# rules of large calls: 920 workgroups (two a CU), 1440 (four a CU), 10240 of
+# short sequences layer by layer, and batches near the most of 256.
+LARGE_CASES = [
+    (1, 300, 16, 8, 128, 1, _MIXED, "bf16", False),
+    (1, 300, 16, 8, 64, 1, _MIXED, "bf16", False),
+    (1, 400, 12, 8, 64, 2, [n for n in _LONG for _ in range(2)], "bf16", False),
+    (64, 40, 8, 8, 64, 1, [1 + 15 * i for i in range(20)], "bf16", False),
+    (1, 80, 16, 2, 128, 4, [(37 * i) % 1201 for i in range(256)], "bf16", False),
+    (1, 160, 16, 1, 64, 2, [(173 * i) % 2501 for i in range(250)], "bf16", False),
+]
+
+
 def case_id(c) -> str:
-    return f"{c[7]}_D{c[4]}_G{c[5]}_bs{c[2]}_ctx{max(c[6])}" + ("_vpos" if c[8] else "")
+    return f"{c[7]}_D{c[4]}_G{c[5]}_bs{c[2]}_ctx{max(c[6])}" + ("_vpos" if c[8] else "") + (
+        f"_L{c[0]}_B{len(c[6])}" if len(c[6]) > 8 else "")
 
 
 def case_seed(c) -> int:
@@ -158,11 +215,14 @@ def abs_v_pool(pool: HostPool) -> HostPool:
     return HostPool(pool.k, v, pool.block_size, pool.slot_bytes)
 
 
-def depth(n):
-    """Longest chain of fp32 additions behind an output of an n-token
-    sequence (see the module docstring)."""
-    n = np.asarray(n, np.float64)
-    return 16.0 + 2.0 * np.ceil(np.minimum(n, PART_TOKENS) / 64.0) + 4.0 + np.ceil(n / PART_TOKENS)
+def depth(ctx, num_layers: int, kv_heads: int, head_dim: int, workspace: str = "full"):
+    """Longest chain of fp32 additions behind an output of each sequence (see
+    the module docstring)."""
+    out = []
+    for parts in partitions(ctx, num_layers, kv_heads, head_dim, workspace):
+        k, sub = len(parts), 1024 // head_dim
+        out.append(32 + -(-max(e - t for t, e in parts) // 64) + 4 + (k if k <= 8 else -(-k // sub) + sub))
+    return np.asarray(out, np.float64)
 
 
 def weight_sum(pool: HostPool, kv_heads: int, head_dim: int, dtype: str, q, tables, ctx, scale):
@@ -188,12 +248,14 @@ def weight_sum(pool: HostPool, kv_heads: int, head_dim: int, dtype: str, q, tabl
     return out
 
 
-def tolerance(orc, pool: HostPool, kv_heads: int, head_dim: int, dtype: str, q, tables, ctx, scale):
+def tolerance(orc, pool: HostPool, kv_heads: int, head_dim: int, dtype: str, q, tables, ctx, scale,
+              workspace: str = "full"):
     """Per-element bound on |kernel - oracle| (see the module docstring)."""
+    chain = depth(ctx, len(q), kv_heads, head_dim, workspace)[None, :, None, None]
     A = orc.decode_attention(abs_v_pool(pool), kv_heads, head_dim, dtype, q, tables, ctx, scale)
     S = scale * np.abs(decode16(q, dtype)).sum(axis=-1, keepdims=True)          # [L][B][Hq][1]
     n = np.asarray(ctx, np.float64)[None, :, None, None]
-    rel = EPS_P[dtype] + LAMBDA * U32 * (2.0 * np.sqrt(depth(n)) + 4.0 * (math.sqrt(head_dim) + 2.0) * S + 2.0)
+    rel = EPS_P[dtype] + LAMBDA * U32 * (2.0 * np.sqrt(chain) + 4.0 * (math.sqrt(head_dim) + 2.0) * S + 2.0)
     if dtype == "fp16":
         W = weight_sum(pool, kv_heads, head_dim, dtype, q, tables, ctx, scale)
         lo = LAMBDA * np.sqrt(n) * U32 / 2 / W
@@ -205,15 +267,6 @@ def tolerance(orc, pool: HostPool, kv_heads: int, head_dim: int, dtype: str, q, 
 def excess(got, want, tol) -> np.ndarray:
     """|got - want| / tol: the bound holds where this is at most 1."""
     return np.abs(np.asarray(got, np.float64) - want) / tol
-
-
-def items(ctx):
-    """The (sequence, first token, end token) items of a call, in launch order."""
-    out = []
-    for b, n in enumerate(ctx):
-        for t in range(0, n, PART_TOKENS):
-            out.append((b, t, min(n, t + PART_TOKENS)))
-    return out
 
 
 def drop_tokens(tables, ctx, block_size: int, b: int, lo: int, hi: int):

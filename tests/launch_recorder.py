@@ -40,7 +40,7 @@ class ConvertArgs(ctypes.Structure):
 class AttnArgs(ctypes.Structure):
     _fields_ = [("k_tab", P), ("q", P), ("tables", P), ("ws", P), ("out", P), ("scale", ctypes.c_float),
                 ("num_layers", U32), ("batch", U32), ("q_heads", U32), ("kv_heads", U32), ("block_size", U32),
-                ("table_stride", U32), ("item_base", U32), ("n_records", U32), ("part_tokens", U32),
+                ("table_stride", U32), ("item_base", U32), ("layer_items", U32), ("n_records", U32), ("part_tokens", U32),
                 ("item_end", U32 * MAX_BATCH), ("ctx", I32 * MAX_BATCH), ("seq", U32 * (MAX_BATCH // 2)),
                 ("dst_tab", P), ("mig_ids", P), ("mig_seq", I32), ("mig_from", I32), ("mig_to", I32),
                 ("dst_layer_bytes", U32), ("dst_blocks", I32)]

@@ -11,6 +11,7 @@ import sys
 import numpy as np
 import pytest
 
+import attn_cases
 from paper_2406_03243_amd.build import LIBRARY
 
 TESTS = os.path.dirname(os.path.abspath(__file__))
@@ -183,6 +184,9 @@ def test_attention_partitions_cover_every_token(record):
         for b, n in enumerate(c["ctx"]):
             assert parts[b][0][0] == 0 and parts[b][-1][1] == n
             assert all(x[1] == y[0] and y[0] % 64 == 0 for x, y in zip(parts[b], parts[b][1:]))
+        layers, _, _, heads, dim = c["pool_args"]
+        assert [parts[b] for b in range(len(c["ctx"]))] == attn_cases.partitions(c["ctx"], layers, heads, dim,
+                                                                                 c["workspace"])
 
 
 def test_attention_runs_as_several_launches(record):
@@ -264,3 +268,13 @@ def test_attention_of_long_partitions_leaves_room(record):
             assert lds == 0, (pool, ctx, workgroups)
         else:
             assert 163840 // (static[pool[4]] + lds) == want, (pool, ctx, workgroups, lds)
+
+
+def test_many_short_sequences_of_head_dim_64_run_layer_by_layer(record):
+    calls = [((128, 8, 16, 32, 64), [20] * 2, True), ((127, 8, 16, 32, 64), [20] * 2, False),
+             ((128, 8, 16, 32, 64), [199] * 2, True), ((128, 8, 16, 32, 64), [200] * 2, False),
+             ((128, 8, 16, 32, 128), [20] * 2, False), ((256, 8, 16, 256, 64), [20] * 200, True)]
+    for (pool, ctx, want), got in zip(calls, record([decode(p, c) for p, c, _ in calls])):
+        partitions(got["launches"])
+        for x in got["launches"]:
+            assert x["layer_items"] == (x["grid"] // (pool[0] * pool[3]) if want else 0)

@@ -54,7 +54,7 @@ def _run(case, seed):
     want = orc.decode_attention(host, kv_heads, head_dim, dtype, qbits, tables, ctx, scale)
     tol = ac.tolerance(orc, host, kv_heads, head_dim, dtype, qbits, tables, ctx, scale)
     ratio = ac.excess(got_h, want, tol)
-    say(f"items {len(ac.items(ctx))} x {num_layers} layers: bit-identical to the workspace call, "
+    say(f"{sum(map(len, ac.partitions(ctx, num_layers, kv_heads, head_dim)))} partitions x {num_layers} layers: bit-identical to the workspace call, "
         f"max error / bound {ratio.max():.3g}")
     assert (ratio <= 1.0).all()
 
