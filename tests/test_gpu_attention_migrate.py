@@ -13,8 +13,8 @@ Every case checks, through the C ABI, against the oracle:
   * the source pool, unchanged.
 Cases cover head dims 64 and 128, block sizes 1-32, grouped and ungrouped
 heads, stages that start inside a partition and end inside another,
-sequences of several 2048-token partitions, a call split over two launches
-with the migrating sequence in both, and seeded random shapes."""
+sequences of one and of several partitions, short ones and ones of up to 2048
+tokens, and seeded random shapes."""
 import sys
 
 import numpy as np
@@ -118,19 +118,23 @@ def run_case(case, seq, from_block, to_block, seed, extra_dst_blocks=7):
 CASES = [
     (ac.CASES[0], 2, 0, 37),          # 600 tokens: all 37 full blocks, D 128, 8 heads a group
     (ac.CASES[1], 0, 5, 32),          # starts inside the partition, D 64
-    (ac.CASES[2], 0, 0, 256),         # two partitions of 2048
-    (ac.CASES[2], 0, 100, 200),       # a range across the partition boundary
+    (ac.CASES[2], 0, 0, 256),         # several partitions
+    (ac.CASES[2], 0, 100, 200),       # a range across partition edges
     (ac.CASES[3], 1, 3, 11),          # 8-token blocks, 4 sequences
-    (ac.CASES[5], 1, 100, 7500),      # 133 items, two launches: sequence 1 spans both
+    (ac.CASES[5], 1, 100, 7500),      # partitions of over 1000 tokens
     (ac.CASES[7], 2, 0, 15),          # 4-token blocks
     (ac.CASES[9], 1, 0, 625),         # 32-token blocks, ten partitions
     (ac.CASES[6], 0, 42, 43),         # the last whole block of 700 tokens, 16 query heads on one KV head
     (ac.CASES[0], 2, 30, 38),         # ends in the partly filled last block (600 tokens: 8 in block 37)
     (ac.CASES[3], 1, 0, 12),          # 95 tokens in 8-token blocks: the whole request, last block 7/8 full
     (ac.CASES[7], 2, 10, 16),         # 62 tokens in 4-token blocks: the last block half full
-    (ac.CASES[5], 2, 1000, 1250),     # 20000 tokens, a sequence spanning both launches, last block full
+    (ac.CASES[5], 2, 1000, 1250),     # 20000 tokens, last block full
     ((1, 2100, 1, 2, 64, 4, [2050, 7], "fp16", False), 0, 1000, 2050),   # 1-token blocks across a partition edge
     ((2, 200, 32, 2, 128, 8, [1000, 70], "bf16", False), 0, 20, 32),     # 32-token blocks, last one 8/32 full
+    (ac.LARGE_CASES[0], 29, 0, 293),  # 4680 tokens in three partitions of over 1500, the last block half full
+    (ac.LARGE_CASES[0], 30, 7, 120),  # a whole sequence of 2000
+    (ac.LARGE_CASES[1], 0, 3, 256),
+    (ac.LARGE_CASES[2], 6, 0, 347),   # 12-token blocks, the last one 8/12 full
 ]
 
 
