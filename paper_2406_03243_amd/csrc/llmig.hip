@@ -68,7 +68,7 @@ namespace {
 //  * write_slabs (convert_tiles.h), other layouts from kSlabWriteTokens tokens
 //    on: a head's slab of a block goes through LDS, so the stores are whole
 //    chunks in the tile's own order.
-//  * write_token_slots, the rest (a few tokens; slabs over 16 KiB; HDN with
+//  * write_token_slots, the rest (appends of a few tokens; slabs over 16 KiB; HDN with
 //    a block size that 8 does not divide): a token and tensor per workgroup,
 //    16-byte loads, stores where the layout puts each piece (HDN: 2 bytes at
 //    a time).
@@ -201,12 +201,16 @@ __global__ void __launch_bounds__(64) signal_host(uint64_t *slot, uint64_t ticke
         __hip_atomic_store(slot, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Token-major writes up to this size (what decoding appends), of slots that
-// fill a workgroup, keep a token and tensor per workgroup: beside a migration's
-// first stage their few workgroups and cached stores cost the stage less (a
-// migration of 8192 + 4 x 37 tokens of a 7B shape 1363-1368 us against
-// 1376-1381 with rows).
-constexpr int64_t kSmallWriteBytes = 32 << 20;
+// Token-major writes of up to this many tokens (what a request decodes between
+// two stages), of slots that fill half a workgroup, keep a token and tensor per
+// workgroup: beside a migration's first stage their few workgroups and cached
+// stores cost the stage less.  A migration of 6000-8192 tokens with four
+// appends, slots / rows: 37 tokens, 32 layers of 32 heads 1372 / 1386 us, 80
+// of 8 681 / 697; 64 tokens 1394 / 1414 and 696 / 716 (two of 200: 708 / 729).
+// By themselves rows are faster from 20 MB on: 80 layers of 8 heads, 61 tokens
+// 10.6 / 8.9 us, 183 24.8 / 20.2; 32 of 32, 57 tokens 11.7 / 11.4, 228 45 / 37;
+// level below (122 tokens of 8 layers of 8 heads 9.0 / 8.9).
+constexpr int64_t kAppendTokens = 64;
 
 // From this many tokens on a write to a pool that is not token-major goes
 // slab by slab (32 layers of 32 heads, HCNX/HDN: 2 tokens 9.2 -> 8.8 us, 4
@@ -995,7 +999,7 @@ int llmig_write_tokens(const llmig_pool *pool, const int32_t *table, int64_t tab
     a.layouts[1] = pool->layouts[1];
     a.data_tokens = static_cast<uint32_t>(n_tok);
     const int64_t planes = 2ll * pool->num_layers;
-    const bool rows = nhd && (slot_bytes < kRowBytes / 2 || n_tok * slot_bytes > kSmallWriteBytes / planes) &&
+    const bool rows = nhd && (slot_bytes < kRowBytes / 2 || n_tok > kAppendTokens) &&
                       bs * slot_bytes / 1024 < 0x3fffffffll / planes / kInlinePairs;
     const bool slabs = !nhd && n_tok >= kSlabWriteTokens && conversion_supported(pool, pool->layouts) &&
                        planes * pool->num_kv_heads * kInlinePairs < 0x7fffffffll;

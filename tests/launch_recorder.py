@@ -52,7 +52,15 @@ class AttnReduceArgs(ctypes.Structure):
                 ("seq", ctypes.c_uint8 * MAX_BATCH)]
 
 
-STRUCTS = {"attn_partial_mfma": AttnArgs, "attn_reduce": AttnReduceArgs, "copy_rows": CopyArgs, "copy_tiles": CopyArgs, "convert_slabs": ConvertArgs, "convert_tiles": ConvertArgs}
+class WriteArgs(ctypes.Structure):
+    _fields_ = [("tab", P), ("data", P), ("slot_bytes", U32), ("tile_bytes", U32), ("block_size", U32),
+                ("num_layers", U32), ("head_dim", U32), ("row_chunks", U32), ("layouts", I32 * 2),
+                ("data_tokens", U32), ("first_token", U32), ("tokens", U32), ("first_slot", U32), ("blocks", U32),
+                ("rows_per_run", U32), ("first_item", U32), ("by_row", Divisor), ("by_block", Divisor),
+                ("ids", I32 * INLINE)]
+
+
+STRUCTS = {"write_rows": WriteArgs, "write_token_slots": WriteArgs, "write_slabs": ConvertArgs, "attn_partial_mfma": AttnArgs, "attn_reduce": AttnReduceArgs, "copy_rows": CopyArgs, "copy_tiles": CopyArgs, "convert_slabs": ConvertArgs, "convert_tiles": ConvertArgs}
 
 
 class Desc(ctypes.Structure):
@@ -147,12 +155,21 @@ def decode(pool_args, ctx, group, workspace="full"):
                                       ctypes.c_int64(size.value if workspace == "full" else least), out, None)
 
 
+def write(pool_args, table, first, tokens, layouts=(0, 0)):
+    t, pt, n = ids(table)
+    return lib.llmig_write_tokens(pool(*pool_args, layouts), pt, n, ctypes.c_int64(first), ctypes.c_int64(tokens),
+                                  ctypes.c_void_p(1 << 30), None)
+
+
+CALLS = {"stage": stage, "decode": decode, "write": write}
+
+
 def main():
     out = []
     for c in json.load(sys.stdin):
         launches.clear()
         kind = c.pop("call")
-        rc = {"stage": stage, "decode": decode}[kind](**c) if kind in ("stage", "decode") else fuse(kind, **c)
+        rc = CALLS[kind](**c) if kind in CALLS else fuse(kind, **c)
         out.append({"rc": rc, "launches": list(launches)})
     json.dump(out, sys.stdout)
 

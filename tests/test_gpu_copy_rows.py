@@ -131,7 +131,9 @@ WRITE_CASES = [
     (1, 20, 32, 3, 128, 9, 200),     # partial 8-token units on both ends
     (1, 20, 12, 3, 64, 7, 100),      # HDN with a block size that 8 does not divide
     (1, 6, 128, 2, 128, 100, 400),   # slabs over 16 KiB
-    (1, 140, 16, 32, 128, 5, 2060),  # over 32 MiB of 8 KiB slots
+    (1, 140, 16, 32, 128, 5, 2060),  # a prompt of 8 KiB slots
+    (2, 12, 16, 8, 128, 9, 64),      # the longest append of 2 KiB slots
+    (2, 12, 16, 8, 128, 9, 65),      # the shortest prompt
 ]
 
 

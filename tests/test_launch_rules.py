@@ -114,6 +114,39 @@ def test_pairs_are_ordered_only_where_it_pays(record, call):
             assert pairs == list(zip(src, dst)), (pool, n)
 
 
+# pool, layouts, first token, tokens, the kernel that writes them
+WRITES = [((80, 300, 16, 32, 128), (0, 0), 3, 64, "write_token_slots"),     # appends, whatever their bytes
+          ((1, 300, 16, 8, 128), (0, 0), 3, 65, "write_rows"),
+          ((80, 300, 16, 8, 128), (0, 0), 0, 4800, "write_rows"),
+          ((2, 300, 16, 7, 128), (0, 0), 0, 1, "write_rows"),               # slots under 2 KiB
+          ((2, 300, 16, 8, 128), (2, 3), 0, 1, "write_token_slots"),
+          ((2, 300, 16, 8, 128), (2, 3), 15, 2, "write_slabs"),
+          ((2, 300, 16, 8, 128), (0, 1), 0, 4700, "write_slabs"),
+          ((2, 300, 12, 8, 128), (2, 3), 0, 100, "write_token_slots"),      # HDN, 8 does not divide the block
+          ((2, 300, 256, 8, 128), (1, 1), 0, 100, "write_token_slots")]     # slabs over 16 KiB
+
+
+def test_token_writes(record):
+    """The kernel of a write, and that its launches cover every token once."""
+    for (pool, layouts, first, n, kernel), got in zip(WRITES, record([
+            dict(call="write", pool_args=p, table=list(range(300)), first=f, tokens=n, layouts=l) for p, l, f, n, _ in WRITES])):
+        assert got["rc"] == 0 and {x["kernel"] for x in got["launches"]} == {kernel}, (pool, layouts, n)
+        at = 0
+        for x in got["launches"]:
+            assert x["lin_first" if kernel == "write_slabs" else "first_token"] == at
+            assert x["first_slot"] == (first + at) % pool[2]
+            blocks = x["pairs" if kernel == "write_slabs" else "blocks"]
+            assert blocks == (first + at + x["tokens"] - 1) // pool[2] - (first + at) // pool[2] + 1 <= 256
+            assert x["ids"][:blocks] == list(range((first + at) // pool[2], (first + at) // pool[2] + blocks))
+            if kernel == "write_rows":
+                run = min(pool[2], x["tokens"]) * x["slot_bytes"]
+                assert x["rows_per_run"] == -(-run // 1024) and x["grid"] == blocks * 2 * pool[0] * x["rows_per_run"]
+            elif kernel == "write_slabs":
+                assert x["grid"] == blocks * 2 * pool[0] * pool[3]
+            at += x["tokens"]
+        assert at == n
+
+
 # ---- decode attention ---------------------------------------------------------
 
 def partitions(launches):
