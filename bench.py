@@ -64,17 +64,6 @@ def recorded_traffic(kernel: str):
     return rec["traffic_bytes_per_launch"]
 
 
-def bulk_span_rows(tile_bytes: int) -> int:
-    """The span (1 KiB rows per wavefront) of a bulk launch under a workgroup
-    cap: the power of two at or above a quarter of the tile, within [2, 32]
-    (mirrors the library's launch configuration, for labelling only)."""
-    quarter = -(-tile_bytes // 4096)
-    span = 2
-    while span < 32 and span < quarter:
-        span *= 2
-    return span
-
-
 def percentile(xs, q):
     """The q-th percentile (0-100) of xs, linear between order statistics."""
     v = sorted(xs)

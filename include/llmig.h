@@ -375,6 +375,11 @@ int llmig_stream_read(const void *region, int64_t bytes, int32_t passes, int32_t
  * aligned.  (That size lets a small call be cut finely enough to use the
  * whole chip.  A call also takes any size that holds, per layer and query
  * head, head_dim + 4 floats for each 2048 tokens begun of every sequence.)
+ * How a sequence is cut, and with it the rounding of its results (fp32 sums
+ * in another order), depends on the whole call: its lengths, layers and
+ * heads, and whether the workspace holds a finer cut.  Equal calls with
+ * workspaces of the returned size, or through the entry points below, give
+ * equal bits.
  * Supported: NHD pools, head_dim 64 or 128, q_heads / num_kv_heads in
  * {1, 2, 4, 8, 16}, batch <= 256; else LLMIG_EINVAL.  Arithmetic in fp32. */
 int llmig_decode_attention_workspace(const int32_t *ctx_lens, int32_t batch, int32_t num_layers,

@@ -38,9 +38,10 @@
 //    from 8 source chunks.  The LDS image has one 16-byte pad after every 16
 //    chunks, which spreads the strided reads of both cases over distinct
 //    banks for the common shapes (block_size 16, head_dim 64 or 128).
-//  * A plane whose two layouts agree (say K converts and V does not), and
-//    one between NHD and HND (whose slabs hold their chunks in one order),
-//    moves chunk for chunk, registers straight to the store, without LDS.
+//  * A plane whose two layouts agree (say K converts and V does not) moves
+//    chunk for chunk, registers straight to the store, without LDS; so does,
+//    in convert_slabs, one between NHD and HND, whose slabs hold their chunks
+//    in one order.
 //  * convert_tiles, launches under a workgroup cap (the throttle of a
 //    migration's non-final stages): few resident workgroups, so each
 //    wavefront keeps a whole slab in flight.  Two wavefronts per workgroup

@@ -180,7 +180,8 @@ __global__ void __launch_bounds__(kThreads) attn_reduce(const AttnReduceArgs a)
 //             requested as soon as this group's operands have been read out
 //             of LDS, so they are in flight while this group computes, and
 //             no registers hold rows in transit;
-//   S^T = K . Q^T     16 tokens x 16 query rows (the group's heads, zero-padded),
+//   S^T = K . Q^T     16 tokens x 16 query rows (the group's heads, then its
+//                     last head again, whose results go nowhere),
 //                     16x16x32 MFMA over head_dim in steps of 32; the K rows
 //                     sit in LDS with their 16-byte chunks XOR-swizzled by
 //                     token, so the operand reads (token = lane % 16) hit
@@ -196,9 +197,13 @@ __global__ void __launch_bounds__(kThreads) attn_reduce(const AttnReduceArgs a)
 //                     keep ~2^-16 (bf16) / 2^-22 (fp16) precision.
 // The four wavefronts take alternate token groups of the partition and merge
 // their states through LDS at the end.  The kernel waits on HBM, not on the
-// matrix cores or LDS, so it is built for four wavefronts per SIMD (at most
-// 128 registers: the accumulators move from AGPRs to VGPRs; 32 KiB of LDS
-// per workgroup for the rows).
+// matrix cores or LDS, so it is built for at least four wavefronts per SIMD (at
+// most 128 registers: the accumulators move from AGPRs to VGPRs; 33.5 KiB of
+// LDS per workgroup for the rows and the merge, 17.5 for head_dim 64).  The
+// carrying variant asks for three only: it also holds the stage's rows between
+// LDS and their stores (163 registers for head_dim 128), and at four the
+// compiler spills 40 to 52 of them, whose loads and stores the counted wait of
+// the loop does not expect.
 // What a workgroup spends besides its loop is what bounds short sequences:
 // each dependent access costs the latency of a loaded memory system (~5 us
 // with every CU's 128 KiB in flight).  So the block ids are one load per lane
@@ -206,11 +211,12 @@ __global__ void __launch_bounds__(kThreads) attn_reduce(const AttnReduceArgs a)
 // short ones), a sequence of one partition needs no record and no merge, and
 // results leave in whole rows at device scope.  Measured on MI355X against
 // partitions in batch order, layer by layer, ids staged behind a barrier,
-// every result through a record and the merge, scattered 64-byte stores: 32
-// layers of 32 heads, 8 sequences of 200-1500 tokens, 752 -> 505 us (4.34 ->
-// 6.46 TB/s); 64 of 40-300, 899 -> 789; 80 layers of 8 heads (64 query
-// heads), 16 of 550-4096, 1498 -> 1255 (5.03 -> 6.0 TB/s); 17 of 520-3840,
-// 1846 -> 1670; 32 layers of one sequence of 32000, 701 -> 676.
+// every result through a record and the merge, scattered 64-byte stores
+// (lengths evenly spread): 32 layers of 32 heads, 8 sequences of 200-1500
+// tokens, 729 -> 522 us (4.90 -> 6.84 TB/s); 64 of 40-300, 962 -> 894; 80 layers
+// of 8 heads (64 query heads), 16 of 550-4096, 2048 -> 1926 (6.36 TB/s); 17 of
+// 520-3840, 2214 -> 1925; 32 layers of 8 heads, one sequence of 32000, 691 ->
+// 671.
 // Earlier steps on the same kernel: whole-row K loads rearranged through LDS
 // instead of K fragments loaded straight into the operand layout (16 rows x
 // 64 bytes per load instruction) +8%; grouping each (partition, layer)'s KV
