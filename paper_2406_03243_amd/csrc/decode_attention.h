@@ -867,14 +867,18 @@ inline int32_t attn_part_tokens(const int32_t *ctx_lens, int32_t batch, int64_t 
 // 1248 87 -> 92, 1408 110 -> 117; 1504 gain 7%.  Calls just short of 1024
 // workgroups run as two rounds of two a CU: one layer of 4 heads of 64, 38 of
 // up to 25627 (944) 90 -> 84.5, 8 heads, 28 of up to 14959 (904) 88 -> 75;
-// head_dim 128, 64 of up to 6197 (936) 147 -> 136; 800 workgroups lose 6%.  (The
-// carrying kernel has not been measured so.)
+// head_dim 128, 64 of up to 6197 (936) 147 -> 136; 800 workgroups lose 6%.  A
+// call that carries a stage, whose workgroups differ in length anyway, keeps
+// to the first rule alone: 4 layers of 32 heads of 64, one of 16528 (1152
+// workgroups) 250 us with four a CU, 267 with eight.
 inline int attn_workgroups_per_cu(int64_t head_dim, int64_t workgroups, int64_t mean_tokens, bool migrating)
 {
     const int64_t full = head_dim == 64 ? 4 : 3;
     if (!migrating && workgroups >= 840 && workgroups <= 4 * kAttnCUs && mean_tokens >= 1200)
         return 2;
-    return 5 * workgroups >= 7 * full * kAttnCUs && mean_tokens >= (head_dim == 64 ? 800 : 1500) ? full : 0;
+    if (!migrating && 5 * workgroups < 7 * full * kAttnCUs)
+        return 0;
+    return mean_tokens >= (head_dim == 64 ? 800 : 1500) ? full : 0;
 }
 
 // Whether a call runs layer by layer instead of longest item first: batches of

@@ -197,8 +197,8 @@ def partitions(launches):
     return out, items * per_item
 
 
-def decode(pool, ctx, group=1, workspace="full"):
-    return dict(call="decode", pool_args=pool, ctx=ctx, group=group, workspace=workspace)
+def decode(pool, ctx, group=1, workspace="full", carry=None):
+    return dict(call="decode", pool_args=pool, ctx=ctx, group=group, workspace=workspace, carry=carry)
 
 
 def test_attention_partitions_cover_every_token(record):
@@ -301,6 +301,13 @@ def test_attention_of_long_partitions_leaves_room(record):
             assert lds == 0, (pool, ctx, workgroups)
         else:
             assert 163840 // (static[pool[4]] + lds) == want, (pool, ctx, workgroups, lds)
+    # carrying a stage: by the length of the partitions alone, and cut as the plain call
+    calls = [((4, 2000, 16, 32, 64), [16528], 4), ((4, 2000, 16, 8, 128), [16000] * 4, 3), ((1, 2000, 16, 8, 64), [700], 0)]
+    for (pool, ctx, want), got, plain in zip(calls, record([decode(p, c, carry=9) for p, c, _ in calls]),
+                                             record([decode(p, c) for p, c, _ in calls])):
+        lds = got["launches"][0]["lds"]
+        assert got["rc"] == 0 and (163840 // (static[pool[4]] + lds) if lds else 0) == want
+        assert partitions(got["launches"]) == partitions(plain["launches"])
 
 
 def test_many_short_sequences_of_head_dim_64_run_layer_by_layer(record):
