@@ -73,7 +73,8 @@ constexpr int kConvertWaves = 2;                    // wavefronts per workgroup
 constexpr uint32_t kXcds = 8;                       // accelerator dies the dispatcher deals workgroups to
 constexpr uint32_t kSlabRun = 64;                   // convert_slabs: slabs in a row on one XCD
 
-struct ConvertArgs {
+// What a launch moves between which layouts, without its block ids.
+struct ConvertShape {
     const uint64_t *src_tab;
     const uint64_t *dst_tab;
     const uint8_t *src_lin;     // staging buffer [L][2][lin_pairs][tile] (null: source is a pool)
@@ -98,7 +99,16 @@ struct ConvertArgs {
     uint32_t first_slot;        // write_slabs: slot of the launch's first token in its block
     uint32_t tokens;            // write_slabs: tokens in this launch
     int32_t layouts[4];         // source K, source V, destination K, destination V
+};
+
+struct ConvertArgs : ConvertShape {
     uint32_t ids[2 * kInlinePairs]; // inline ids, laid out as the launch's Ids mode says
+};
+
+// A write lists one block per id; its arguments are half as long (they are
+// copied into the launch: 16 writes of 7 tokens 133.3 -> 131.8 us).
+struct SlabWriteArgs : ConvertShape {
+    uint32_t ids[kInlinePairs];
 };
 
 __device__ __forceinline__ uint32_t div_magic(uint32_t n, uint64_t magic)
@@ -107,7 +117,7 @@ __device__ __forceinline__ uint32_t div_magic(uint32_t n, uint64_t magic)
 }
 
 // Byte offset inside a tile of chunk k (in the layout's own order) of head h.
-__device__ __forceinline__ uint32_t slab_offset(int32_t layout, uint32_t h, uint32_t k, const ConvertArgs &a)
+__device__ __forceinline__ uint32_t slab_offset(int32_t layout, uint32_t h, uint32_t k, const ConvertShape &a)
 {
     if (layout == LLMIG_LAYOUT_NHD) {
         const uint32_t t = div_magic(k, a.magic_row);
@@ -119,7 +129,7 @@ __device__ __forceinline__ uint32_t slab_offset(int32_t layout, uint32_t h, uint
 
 // Slab index of the chunk holding dims [8c, 8c + 8) of token t, in a layout
 // whose chunks run along the dims (NHD, HND, HCNX).
-__device__ __forceinline__ uint32_t dim_chunk_index(int32_t layout, uint32_t t, uint32_t c, const ConvertArgs &a)
+__device__ __forceinline__ uint32_t dim_chunk_index(int32_t layout, uint32_t t, uint32_t c, const ConvertShape &a)
 {
     return layout == LLMIG_LAYOUT_HCNX ? c * a.block_size + t : t * a.row_chunks + c;
 }
@@ -171,7 +181,7 @@ __device__ __forceinline__ u32x4 gather8(const u32x4 *slab, uint32_t first, uint
 // Output chunk k of a slab, gathered from the slab's padded LDS image (in the
 // source's chunk order).
 __device__ __forceinline__ u32x4 gather_chunk(const u32x4 *slab, uint32_t k, int32_t sl, int32_t dl,
-                                              const ConvertArgs &a)
+                                              const ConvertShape &a)
 {
     if (dl == LLMIG_LAYOUT_HDN) {
         // tokens [8 tg, 8 tg + 8) of dim dd
@@ -258,7 +268,7 @@ __global__ void __launch_bounds__(WAVES * 64) convert_slabs(const ConvertArgs a)
 // token's in NHD, HND and HCNX; in HDN it is 8 tokens' and is stored element
 // by element where not all 8 are written.
 template <int WAVES>
-__global__ void __launch_bounds__(WAVES * 64) write_slabs(const ConvertArgs a)
+__global__ void __launch_bounds__(WAVES * 64) write_slabs(const SlabWriteArgs a)
 {
     __shared__ u32x4 lds[68 * WAVES];
     const uint32_t k = threadIdx.x;
@@ -445,7 +455,7 @@ uint64_t magic_for(uint32_t divisor)
     return ((1ull << 32) + divisor - 1) / divisor;
 }
 
-void convert_magic(ConvertArgs &a)
+void convert_magic(ConvertShape &a)
 {
     a.magic_row = magic_for(a.row_chunks);
     a.magic_bs = magic_for(a.block_size);

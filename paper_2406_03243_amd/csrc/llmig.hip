@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cstddef>
 #include <cstdint>
 #include <cstring>
 #include <memory>
@@ -481,9 +482,9 @@ bool conversion_supported(const llmig_pool *pool, const int32_t *other)
     return chunks <= 64 * kMaxSlabChunksPerLane;
 }
 
-ConvertArgs convert_args(const llmig_pool *pool, const int32_t *src_layouts, const int32_t *dst_layouts)
+// Fills everything but the ids.
+void convert_shape(ConvertShape &c, const llmig_pool *pool, const int32_t *src_layouts, const int32_t *dst_layouts)
 {
-    ConvertArgs c;
     std::memset(&c, 0, sizeof(c));
     c.tile_bytes = static_cast<uint32_t>(pool->tile_bytes);
     c.num_layers = static_cast<uint32_t>(pool->num_layers);
@@ -496,7 +497,6 @@ ConvertArgs convert_args(const llmig_pool *pool, const int32_t *src_layouts, con
     c.layouts[1] = src_layouts[1];
     c.layouts[2] = dst_layouts[0];
     c.layouts[3] = dst_layouts[1];
-    return c;
 }
 
 bool pools_compatible(const llmig_pool *src, const llmig_pool *dst)
@@ -516,7 +516,8 @@ int launch_stage(const llmig_pool *src, const llmig_pool *dst, const int32_t *ms
                  const LaunchEvents &ev = LaunchEvents())
 {
     if (!same_layouts(src, dst)) {
-        ConvertArgs c = convert_args(src, src->layouts, dst->layouts);
+        ConvertArgs c;
+        convert_shape(c, src, src->layouts, dst->layouts);
         c.src_tab = src->d_tab;
         c.dst_tab = dst->d_tab;
         const bool ids16 = src->num_blocks <= 65536 && dst->num_blocks <= 65536;
@@ -956,7 +957,8 @@ int llmig_unpack_layout(const llmig_pool *dst, const int32_t *blocks, int64_t n,
         rc = staging_pointer(staging, &lin, &on_host);
         if (rc != LLMIG_OK)
             return rc;
-        ConvertArgs c = convert_args(dst, from, dst->layouts);
+        ConvertArgs c;
+        convert_shape(c, dst, from, dst->layouts);
         c.src_lin = static_cast<const uint8_t *>(lin);
         c.dst_tab = dst->d_tab;
         return launch_convert(c, nullptr, blocks, n, map_on_device != 0, static_cast<hipStream_t>(stream), 0);
@@ -986,7 +988,7 @@ int llmig_write_tokens(const llmig_pool *pool, const int32_t *table, int64_t tab
     if (rc != LLMIG_OK)
         return rc;
     WriteArgs a;
-    std::memset(&a, 0, sizeof(a));
+    std::memset(&a, 0, offsetof(WriteArgs, ids));
     a.tab = pool->d_tab;
     a.data = static_cast<const uint8_t *>(data);
     a.slot_bytes = static_cast<uint32_t>(slot_bytes);
@@ -1003,10 +1005,10 @@ int llmig_write_tokens(const llmig_pool *pool, const int32_t *table, int64_t tab
                       bs * slot_bytes / 1024 < 0x3fffffffll / planes / kInlinePairs;
     const bool slabs = !nhd && n_tok >= kSlabWriteTokens && conversion_supported(pool, pool->layouts) &&
                        planes * pool->num_kv_heads * kInlinePairs < 0x7fffffffll;
-    ConvertArgs c;
+    SlabWriteArgs c;
     if (slabs) {
         const int32_t from[2] = {LLMIG_LAYOUT_NHD, LLMIG_LAYOUT_NHD};
-        c = convert_args(pool, from, pool->layouts);
+        convert_shape(c, pool, from, pool->layouts);
         convert_magic(c);
         c.src_lin = static_cast<const uint8_t *>(data);
         c.dst_tab = pool->d_tab;

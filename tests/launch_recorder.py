@@ -60,13 +60,19 @@ class WriteArgs(ctypes.Structure):
                 ("ids", I32 * INLINE)]
 
 
-STRUCTS = {"write_rows": WriteArgs, "write_token_slots": WriteArgs, "write_slabs": ConvertArgs, "attn_partial_mfma": AttnArgs, "attn_reduce": AttnReduceArgs, "copy_rows": CopyArgs, "copy_tiles": CopyArgs, "convert_slabs": ConvertArgs, "convert_tiles": ConvertArgs}
+STRUCTS = {"write_rows": WriteArgs, "write_token_slots": WriteArgs, "attn_partial_mfma": AttnArgs, "attn_reduce": AttnReduceArgs, "copy_rows": CopyArgs, "copy_tiles": CopyArgs, "convert_slabs": ConvertArgs, "convert_tiles": ConvertArgs}
 
 
 class Desc(ctypes.Structure):
     _fields_ = [(n, I32) for n in ("num_layers", "num_blocks", "block_size", "num_kv_heads", "head_dim", "elem_bytes")] \
         + [("k_ptrs", ctypes.POINTER(U64)), ("v_ptrs", ctypes.POINTER(U64)), ("k_layout", I32), ("v_layout", I32)]
 
+
+class SlabWriteArgs(ctypes.Structure):
+    _fields_ = ConvertArgs._fields_[:-1] + [("ids", U32 * INLINE)]
+
+
+STRUCTS["write_slabs"] = SlabWriteArgs
 
 HOST_MEMORY = 1 << 46
 launches = []
