@@ -10,8 +10,8 @@
 // Two kernels, chosen by whether the caller caps the grid:
 //
 // copy_rows, every uncapped launch.  A call's bytes are a list of 1 KiB rows
-// (64 lanes x 16 bytes); a workgroup is one wavefront and moves one row: one
-// load and one store per lane.
+// (64 lanes x 16 bytes); a wavefront moves one row, one load and one store per
+// lane, and is a workgroup by itself (a small launch: two rows, two wavefronts).
 //  * What bounds it is HBM, and how well DRAM likes the order in which a
 //    launch touches it.  With one row per wavefront the rows in flight at any
 //    time (32 wavefronts a CU, 8 MiB over the chip) are consecutive in the
@@ -41,7 +41,11 @@
 //    52 KiB tiles 4.87 against 5.10 us, of 80 layers of 32 KiB 4.27 against
 //    4.63 us, of 32 layers of 128 KiB 5.03 against 5.09 us; 4000 pairs of 2 KiB
 //    tiles of 2 layers through a staging buffer in HBM, 32 launches, 106
-//    against 110 us).  With the staging buffer in host memory it keeps one:
+//    against 110 us).  Its workgroups are two wavefronts, half as many again to
+//    dispatch: whole finishing passes, each with a write and a stage of one
+//    block of 128 KiB tiles, 19 layers 23.4 -> 22.6 us, 24 layers 24.0 -> 23.2,
+//    28 layers 24.2 -> 23.5; other tiles and staging in HBM level (four
+//    wavefronts: the same).  With the staging buffer in host memory it keeps one:
 //    two were 1-3% slower over the link (six pieces of 2.6 MB of 128 KiB tiles
 //    each way 723 against 702 us, one of 3.9 MB of 16 KiB tiles 216 against
 //    210 us).
@@ -151,12 +155,14 @@ __device__ __forceinline__ uint32_t dst_id(const CopyArgs &a, uint32_t i)
 // Workgroups (rows) in a row on one XCD under xcd_runs: 512 KiB.
 constexpr uint32_t kXcdRun = 512;
 
-// One wavefront per workgroup, one item of ROWS KiB of a tile each.
+// ROWS wavefronts per workgroup, one item of ROWS KiB of a tile each.  (A launch's
+// items are a multiple of its planes, K and V of each layer, so two wavefronts
+// leave none over.  Two rows: a small launch, of less than a round of XCD runs.)
 template <int SRC, int DST, int IDS, int ROWS>
-__global__ void __launch_bounds__(64) copy_rows(const CopyArgs a)
+__global__ void __launch_bounds__(64 * ROWS) copy_rows(const CopyArgs a)
 {
-    uint32_t w = blockIdx.x;
-    if (a.xcd_runs) {
+    uint32_t w = ROWS == 1 ? blockIdx.x : uniform(blockIdx.x * ROWS + threadIdx.x / 64);
+    if (ROWS == 1 && a.xcd_runs) {
         // the dispatcher hands workgroup g to XCD g % 8: renumbered so that
         // the k-th kXcdRun workgroups of an XCD are consecutive items (the
         // grid's tail keeps the plain order)
@@ -189,7 +195,7 @@ __global__ void __launch_bounds__(64) copy_rows(const CopyArgs a)
 
     const __amdgpu_buffer_rsrc_t rs = tile_rsrc(s, a.tile_bytes);
     const __amdgpu_buffer_rsrc_t rd = tile_rsrc(d, a.tile_bytes);
-    const uint32_t first = span * ROWS * kWaveRow, lane_off = threadIdx.x * 16u;
+    const uint32_t first = span * ROWS * kWaveRow, lane_off = (threadIdx.x % 64) * 16u;
     u32x4 r[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
@@ -359,7 +365,7 @@ int launch_copy(CopyArgs a, const int32_t *src_ids, const int32_t *dst_ids, int6
         for (uint32_t at = 0; at < a.items; at += std::min(step, a.items - at)) {
             const uint32_t here = std::min(step, a.items - at);
             a.first_item = at;
-            uint32_t grid = here, threads = 64;
+            uint32_t grid = here / span, threads = 64u * span;  // here: a multiple of 2 for spans of 2
             if (capped) {
                 grid = std::min({(here + kThreads / 64 - 1) / (kThreads / 64), kMaxGridWorkgroups, max_workgroups});
                 threads = kThreads;

@@ -51,12 +51,20 @@ def test_host_staging_copies_move_one_row_a_wavefront(record, call, pool):
 
 @pytest.mark.parametrize("call", ["stage", "pack", "unpack"])
 def test_small_copies_move_two_rows_a_wavefront(record, call):
-    """On the GPU, up to one round of resident wavefronts (8192 rows)."""
+    """On the GPU, up to one round of resident wavefronts (8192 rows), and in
+    workgroups of two wavefronts, which every item fills."""
     where = [dict(src=list(range(n)), dst=list(range(n))) if call == "stage" else
              dict(blocks=list(range(n)), staging="device") for n in (32, 33)]
     one, two = record([dict(call=call, pool_args=(1, 64, 16, 32, 128), **w) for w in where])
-    assert one["launches"][0]["template"][3] == 2 and one["launches"][0]["grid"] == 32 * 2 * 64
-    assert two["launches"][0]["template"][3] == 1 and two["launches"][0]["grid"] == 33 * 2 * 128
+    assert one["launches"][0]["template"][3] == 2 and two["launches"][0]["template"][3] == 1
+    assert one["launches"][0]["items"] == 32 * 2 * 64 and two["launches"][0]["items"] == 33 * 2 * 128
+    assert (one["launches"][0]["grid"], one["launches"][0]["block"]) == (32 * 64, 128)
+    assert (two["launches"][0]["grid"], two["launches"][0]["block"]) == (33 * 2 * 128, 64)
+    # tiles of an odd number of KiB and less than one: still whole workgroups
+    for pool in ((1, 64, 8, 1, 64), (3, 64, 8, 3, 64), (1, 64, 16, 3, 128)):
+        for w in where:
+            for x in record([dict(call=call, pool_args=pool, **w)])[0]["launches"]:
+                assert x["block"] == 128 and x["grid"] * 2 == x["items"]
 
 
 def pairs_of(launches):
