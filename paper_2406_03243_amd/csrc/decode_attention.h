@@ -400,7 +400,10 @@ attn_partial_mfma(const AttnArgs a)
         }
         if (a.layer_items) {
             layer = unit / a.layer_items;
-            item = unit - layer * a.layer_items;
+            // (starting one item later in each layer: the items of a layer go to
+            // the XCDs in turn, and an even batch would give the longest of every
+            // layer to the same one)
+            item = (unit - layer * a.layer_items + layer) % a.layer_items;
         } else {
             item = unit / a.num_layers;
             layer = unit - item * a.num_layers;
@@ -884,8 +887,10 @@ inline int attn_workgroups_per_cu(int64_t head_dim, int64_t workgroups, int64_t 
 // Whether a call runs layer by layer instead of longest item first: batches of
 // many short sequences of head_dim 64, whose neighbours then read and write one
 // layer's tensors (what exactly that saves was not traced).  Longest first ->
-// layer by layer: 73 layers of 32 heads, 5 of up to 208 tokens 66.4 -> 62.0 us,
-// 80 of 4, 60 of up to 394 145 -> 137, 32 of 13, 37 of up to 391 110 -> 103.
+// layer by layer: 80 layers of 8 heads, 38 of up to 120 tokens 89.9 -> 80.4 us,
+// 64 of up to 400 354 -> 321, 46 of 25, 29 of up to 125 117 -> 107, 32 of 32, 24
+// of up to 400 154 -> 144 (176 with the layers' items in one order on the XCDs, 8
+// of up to 400 72 -> 106), 8 of up to 40 level.
 // Elsewhere the end of the launch decides: 73 layers of 4 heads of 64, 32 of up
 // to 633 (mean 280) 14% slower, 80 of 8 heads of 128, 12 of up to 122 (7680
 // workgroups) 51 -> 55, decode steps of long sequences up to 48% slower.

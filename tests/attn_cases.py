@@ -139,6 +139,7 @@ LARGE_CASES = [
     (1, 300, 16, 8, 64, 1, _MIXED, "bf16", False),
     (1, 400, 12, 8, 64, 2, [n for n in _LONG for _ in range(2)], "bf16", False),
     (64, 40, 8, 8, 64, 1, [1 + 15 * i for i in range(20)], "bf16", False),
+    (64, 40, 8, 8, 64, 1, [1 + 15 * i for i in range(16)], "bf16", False),
     (1, 80, 16, 2, 128, 4, [(37 * i) % 1201 for i in range(256)], "bf16", False),
     (1, 160, 16, 1, 64, 2, [(173 * i) % 2501 for i in range(250)], "bf16", False),
 ]
