@@ -1223,7 +1223,7 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
     const uint64_t per_item = static_cast<uint64_t>(a.kv_heads) * a.num_layers;
     const int64_t workgroups = static_cast<int64_t>(items * per_item);
     const int per_cu = attn_workgroups_per_cu(pool->head_dim, workgroups, tokens / items, mig.dst != nullptr);
-    const bool by_layer = attn_layer_by_layer(pool->head_dim, workgroups, tokens / items);
+    const bool by_layer = !mig.dst && attn_layer_by_layer(pool->head_dim, workgroups, tokens / items);
     lds = std::max(lds, attn_spare_lds(pool->head_dim, per_cu));
     const uint32_t step = static_cast<uint32_t>(std::max<uint64_t>(kMaxGridWorkgroups / per_item, 1u));
     for (uint32_t at = 0; at < items; at += std::min(step, items - at)) {

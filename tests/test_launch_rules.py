@@ -326,3 +326,6 @@ def test_many_short_sequences_of_head_dim_64_run_layer_by_layer(record):
         partitions(got["launches"])
         for x in got["launches"]:
             assert x["layer_items"] == (x["grid"] // (pool[0] * pool[3]) if want else 0)
+    # not a launch that carries a stage
+    (got,) = record([decode((128, 8, 16, 32, 64), [20] * 2, carry=1)])
+    assert got["rc"] == 0 and [x["layer_items"] for x in got["launches"]] == [0]
