@@ -901,6 +901,22 @@ inline bool attn_layer_by_layer(int64_t head_dim, int64_t workgroups, int64_t me
     return head_dim == 64 && workgroups >= 8192 && mean_tokens < 200;
 }
 
+// Whether the sequence whose stage a call carries is launched apart, before the
+// others, which then run in the kernel that carries none: many short sequences.
+// A carrying workgroup holds the stage's rows in registers (163 against 120 for
+// head_dim 128, 96 against 74 for 64), so fewer of them share a CU, and of short
+// sequences, all start and end, it is the number in flight that counts.  One
+// launch -> two: 51 layers of 34 heads of 128, 15 of up to 75 tokens 164 -> 143
+// us; 80 of 8, 30 of up to 150 162 -> 153; 28 of 32 heads of 64, 53 of up to 100
+// 166 -> 154; 80 of 8, 25 of up to 120 (16000 workgroups) 70 -> 66.  The second
+// launch costs the end of the first: 80 layers of 8 heads of 128, 12 of up to 240
+// (7680 workgroups) 104 -> 107, 50 of 8, 41 of up to 418 (mean 180) 293 -> 296, 64
+// of up to 1000 1671 -> 1687.
+inline bool attn_carry_apart(int64_t workgroups, int64_t mean_tokens)
+{
+    return workgroups >= 16000 && mean_tokens < 160;
+}
+
 // Dynamic LDS that keeps n workgroups of the partial kernel a CU (160 KiB of
 // LDS; 17.5 KiB a workgroup for head_dim 64, 33.5 for 128).
 inline size_t attn_spare_lds(int64_t head_dim, int n)

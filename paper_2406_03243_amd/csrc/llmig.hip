@@ -1146,6 +1146,7 @@ struct AttnMigration {
     int32_t seq = -1;
     const int32_t *ids = nullptr;
     int32_t from = 0, to = 0;
+    const void *plain = nullptr;    // the kernel of a call that carries none
 };
 
 // Enqueues a checked decode-attention call: the partial kernel over the
@@ -1187,13 +1188,27 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
     a.block_size = static_cast<uint32_t>(pool->block_size);
     a.table_stride = static_cast<uint32_t>(table_stride);
     a.part_tokens = static_cast<uint32_t>(part);
-    // launch order: several partitions first, longest partition first
+    const uint64_t per_item = static_cast<uint64_t>(a.kv_heads) * a.num_layers;
+    int64_t tokens = 0;
+    int32_t longest = 0;
+    for (int32_t b = 0; b < batch; ++b) {
+        tokens += ctx_lens[b];
+        longest = std::max(longest, ctx_lens[b]);
+    }
+    const int64_t n_items = attn_items(ctx_lens, batch, part);
+    const int64_t workgroups = n_items * static_cast<int64_t>(per_item);
+    // launch order: several partitions first, longest partition first; a
+    // sequence launched apart before the others (several partitions stay first)
+    const bool apart = mig.dst && batch > 1 && attn_carry_apart(workgroups, tokens / n_items) &&
+                       (longest <= part || ctx_lens[mig.seq] > part);
     uint64_t key[kAttnMaxBatch];
     for (int32_t b = 0; b < batch; ++b) {
         const uint32_t parts = attn_parts(ctx_lens[b], part);
         const uint64_t len = static_cast<uint64_t>(parts > 1 ? attn_part_len(ctx_lens[b], parts) : ctx_lens[b]);
         key[b] = (parts > 1 ? 0ull : 1ull << 63) | (0x7fffffffull - len) << 32 | static_cast<uint64_t>(b);
     }
+    if (apart)
+        key[mig.seq] = static_cast<uint64_t>(mig.seq);
     std::sort(key, key + batch);
     AttnReduceArgs r;
     std::memset(&r, 0, sizeof(r));
@@ -1217,23 +1232,21 @@ static int attn_enqueue(const llmig_pool *pool, const void *fn, const void *q, i
     size_t lds = pool->block_size % 8 == 0
                      ? 0
                      : attn_blk_slots(a.part_tokens, a.block_size) * sizeof(int32_t) * (mig.dst ? 2 : 1);
-    int64_t tokens = 0;
-    for (int32_t b = 0; b < batch; ++b)
-        tokens += ctx_lens[b];
-    const uint64_t per_item = static_cast<uint64_t>(a.kv_heads) * a.num_layers;
-    const int64_t workgroups = static_cast<int64_t>(items * per_item);
-    const int per_cu = attn_workgroups_per_cu(pool->head_dim, workgroups, tokens / items, mig.dst != nullptr);
-    const bool by_layer = !mig.dst && attn_layer_by_layer(pool->head_dim, workgroups, tokens / items);
+    const int per_cu = attn_workgroups_per_cu(pool->head_dim, workgroups, tokens / n_items, mig.dst != nullptr);
+    const bool by_layer = attn_layer_by_layer(pool->head_dim, workgroups, tokens / n_items);
     lds = std::max(lds, attn_spare_lds(pool->head_dim, per_cu));
     const uint32_t step = static_cast<uint32_t>(std::max<uint64_t>(kMaxGridWorkgroups / per_item, 1u));
-    for (uint32_t at = 0; at < items; at += std::min(step, items - at)) {
-        const uint32_t here = std::min(step, items - at);
+    const uint32_t carried = apart ? a.item_end[0] : items;     // items of the first launches, by fn
+    for (uint32_t at = 0; at < items;) {
+        const uint32_t here = std::min(step, (at < carried ? carried : items) - at);
         a.item_base = at;
-        a.layer_items = by_layer ? here : 0u;
+        a.layer_items = by_layer && !(mig.dst && at < carried) ? here : 0u;
         void *args[] = {&a};
-        hipError_t e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(here * per_item)), dim3(kThreads), args, lds, st);
+        hipError_t e = hipLaunchKernel(at < carried ? fn : mig.plain, dim3(static_cast<uint32_t>(here * per_item)),
+                                       dim3(kThreads), args, lds, st);
         if (e != hipSuccess)
             return hip_error(e);
+        at += here;
     }
     if (r.seqs == 0)
         return LLMIG_OK;
@@ -1331,6 +1344,7 @@ int llmig_decode_attention_migrate(const llmig_pool *pool, int32_t dtype, const 
     mig.ids = dst_ids;
     mig.from = static_cast<int32_t>(from_block);
     mig.to = static_cast<int32_t>(to_block);
+    mig.plain = attn_kernel_for(dtype, pool->head_dim, q_heads / pool->num_kv_heads, false, pool->block_size % 8 == 0);
     return attn_enqueue(pool, fn, q, batch, q_heads, tables, table_stride, ctx_lens, scale,
                         static_cast<float *>(workspace), workspace_bytes, out, static_cast<hipStream_t>(stream), mig);
 }

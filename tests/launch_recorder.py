@@ -142,10 +142,10 @@ def fuse(call, pool_args, blocks, staging, layouts=(0, 0), staging_layouts=(0, 0
     return getattr(lib, "llmig_" + call)(p, pa, n, 0, where, size, None)
 
 
-def decode(pool_args, ctx, group, workspace="full", carry=None):
+def decode(pool_args, ctx, group, workspace="full", carry=None, seq=0):
     """workspace: "full" (the size the library returns), "least" (2048 tokens a
     partition), "none" (llmig_decode_attention_noalloc).  carry: blocks of
-    sequence 0 that the call carries into another pool."""
+    sequence `seq` that the call carries into another pool."""
     layers, _, bs, heads, dim = pool_args
     c, pc, _ = ids(ctx)
     q_heads, stride = heads * group, max(1, max(-(-n // bs) for n in ctx))
@@ -161,7 +161,7 @@ def decode(pool_args, ctx, group, workspace="full", carry=None):
     if carry:
         return lib.llmig_decode_attention_migrate(
             pool(*pool_args), 0, q, len(ctx), q_heads, tables, stride, pc, scale, ws, size, out,
-            pool(*pool_args, (0, 0), 2), 0, ctypes.c_void_p(5 << 44), ctypes.c_int64(0), ctypes.c_int64(carry), None)
+            pool(*pool_args, (0, 0), 2), seq, ctypes.c_void_p(5 << 44), ctypes.c_int64(0), ctypes.c_int64(carry), None)
     return lib.llmig_decode_attention(pool(*pool_args), 0, q, len(ctx), q_heads, tables, stride, pc, scale, ws,
                                       ctypes.c_int64(size.value if workspace == "full" else least), out, None)
 

@@ -135,6 +135,13 @@ CASES = [
     (ac.LARGE_CASES[0], 30, 7, 120),  # a whole sequence of 2000
     (ac.LARGE_CASES[1], 0, 3, 256),
     (ac.LARGE_CASES[2], 6, 0, 347),   # 12-token blocks, the last one 8/12 full
+    # many short sequences, the carried one launched apart from the others (and, of
+    # one kind, a sequence fewer: not apart)
+    ((64, 280, 8, 4, 128, 2, [k % 16 for k in range(62)] + [37], "bf16", False), 62, 0, 5),     # the last block 5/8 full
+    ((64, 280, 8, 4, 128, 2, [k % 16 for k in range(61)] + [37], "bf16", False), 61, 0, 5),
+    ((64, 160, 12, 4, 64, 1, [7] + [k % 23 for k in range(63)], "fp16", False), 0, 0, 1),       # a short one; layer by layer
+    ((33, 840, 8, 2, 64, 8, [k % 9 for k in range(248)] + [2500, 2100], "fp16", False), 249, 3, 263),  # cut in two
+    ((33, 840, 8, 2, 64, 8, [k % 9 for k in range(248)] + [2500, 2100], "fp16", False), 3, 0, 1),         # beside cut ones
 ]
 
 

@@ -160,8 +160,9 @@ def test_token_writes(record):
 def partitions(launches):
     """{sequence: [(first token, end)]} of a call as its kernels will number
     them, and its workgroups, checked: sequences of several partitions come
-    first, longest partition first, launches cover every item once, and the
-    merge reads the records the partial kernel leaves."""
+    first, longest partition first (after a sequence that carries a stage and is
+    launched apart), launches cover every item once, and the merge reads the
+    records the partial kernel leaves."""
     partial = [x for x in launches if x["kernel"] == "attn_partial_mfma"]
     a = partial[0]
     per_item = a["kv_heads"] * a["num_layers"]
@@ -180,7 +181,8 @@ def partitions(launches):
         lengths.append((parts == 1, -(plen if parts > 1 else n)))
         assert max(e - t for t, e in out[b]) <= a["part_tokens"] <= 2048
         first = end
-    assert lengths == sorted(lengths)
+    apart = len({x["template"][2] for x in partial}) == 2
+    assert lengths[apart:] == sorted(lengths[apart:]) and lengths[0][0] <= lengths[-1][0]
     assert a["n_records"] == sum(len(p) for p in out.values() if len(p) > 1)
     items, at = first, 0
     for x in partial:
@@ -205,8 +207,8 @@ def partitions(launches):
     return out, items * per_item
 
 
-def decode(pool, ctx, group=1, workspace="full", carry=None):
-    return dict(call="decode", pool_args=pool, ctx=ctx, group=group, workspace=workspace, carry=carry)
+def decode(pool, ctx, group=1, workspace="full", carry=None, seq=0):
+    return dict(call="decode", pool_args=pool, ctx=ctx, group=group, workspace=workspace, carry=carry, seq=seq)
 
 
 def test_attention_partitions_cover_every_token(record):
@@ -329,3 +331,34 @@ def test_many_short_sequences_of_head_dim_64_run_layer_by_layer(record):
     # not a launch that carries a stage
     (got,) = record([decode((128, 8, 16, 32, 64), [20] * 2, carry=1)])
     assert got["rc"] == 0 and [x["layer_items"] for x in got["launches"]] == [0]
+
+
+# pool, lengths, the sequence whose blocks are carried, whether it is launched apart
+APART = [((40, 300, 16, 20, 128), [30] * 19 + [41], 7, True), ((40, 300, 16, 20, 128), [30] * 18 + [41], 7, False),
+         ((40, 300, 16, 20, 64), [30] * 19 + [41], 19, True), ((40, 300, 16, 20, 64), [30] * 18 + [41], 0, False),
+         ((40, 300, 16, 20, 128), [159] * 20, 0, True), ((40, 300, 16, 20, 128), [160] * 20, 0, False),
+         ((200, 300, 12, 100, 128), [30], 0, False),                    # alone
+         ((80, 300, 16, 4, 128), [5, 0, 17] * 30 + [4097, 2100], 91, True),     # cut, after a longer one
+         ((80, 300, 16, 4, 128), [5, 0, 17] * 30 + [4097, 2100], 90, True),
+         ((80, 300, 16, 4, 128), [5, 0, 17] * 30 + [4097, 2100], 0, False),     # whole, beside cut ones
+         ((256, 300, 16, 256, 64), [20] * 200, 199, True)]              # several launches of the others
+
+
+def test_the_sequence_a_call_of_many_short_ones_carries_is_launched_apart(record):
+    for (pool, ctx, seq, apart), got, plain in zip(APART, record([decode(p, c, carry=1, seq=s) for p, c, s, _ in APART]),
+                                                   record([decode(p, c) for p, c, _, _ in APART])):
+        what = (pool, ctx[:3], seq)
+        assert got["rc"] == 0, what
+        parts, workgroups = partitions(got["launches"])
+        assert (parts, workgroups) == partitions(plain["launches"]), what
+        per_item = pool[0] * pool[3]
+        partial = [x for x in got["launches"] if x["kernel"] == "attn_partial_mfma"]
+        carrying = [x for x in partial if x["template"][2] == 1]
+        assert all(x["mig_seq"] == seq and x["template"][3] == (pool[2] % 8 == 0) for x in partial), what
+        if apart:
+            assert partial[0] is carrying[0] and len(carrying) == 1 and len(partial) >= 2, what
+            assert carrying[0]["grid"] == len(parts[seq]) * per_item and list(parts)[0] == seq, what
+            assert carrying[0]["layer_items"] == 0, what
+            assert all(x["layer_items"] == (x["grid"] // per_item if pool[4] == 64 else 0) for x in partial[1:]), what
+        else:
+            assert len(carrying) == len(partial), what
